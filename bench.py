@@ -178,7 +178,7 @@ def measured_traffic(workload):
     it is now."""
     import hashlib
     path = os.path.join(ROOT, "profiles", f"gemm_traffic_{workload}.json")
-    src = os.path.join(ROOT, "paper_2509_16248_amd", "csrc", "gm_gemm.hip")
+    src = os.path.join(ROOT, "paper_2509_16248_amd", "csrc", "gm_gemm_tile.h")
     try:
         rec = json.load(open(path))
         sha = hashlib.sha256(open(src, "rb").read()).hexdigest()

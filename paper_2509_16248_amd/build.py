@@ -27,13 +27,21 @@ COMMON = ["-O3", "-fPIC", "-std=c++17", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wno-unused-command-line-argument"]
 
-SOURCES = ["gm_rows.hip", "gm_gemm.hip", "gm_attention.hip", "gm_decode.hip", "gm_runtime.cpp"]
+# (source, defines): gm_gemm_16bit.hip holds large kernels and is compiled in
+# parts (storage type x group of tile shapes)
+SOURCES = ([("gm_gemm_16bit.hip", {"GM_T": t, "GM_GROUP": g}) for t in (0, 1) for g in range(4)]
+           + [(s, {}) for s in ("gm_rows.hip", "gm_gemm.hip", "gm_gemm_f32.hip",
+                                "gm_gemm_skinny.hip", "gm_attention.hip", "gm_decode.hip",
+                                "gm_runtime.cpp")])
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.basename(src) + ".o")
+def _compile(unit) -> str:
+    src, defines = unit
+    tag = "".join(f".{v}" for v in defines.values())
+    obj = os.path.join(OBJ, os.path.basename(src) + tag + ".o")
     lang = ["-x", "hip"] if src.endswith(".cpp") else []
-    cmd = [HIPCC, *COMMON, *lang, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *COMMON, *[f"-D{k}={v}" for k, v in defines.items()], *lang, "-c",
+           os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")

@@ -662,21 +662,12 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
     P(GM_K_ARGMAX, -1, 0.0, es * B * static_cast<double>(c.vocab));
   }
   };
-  // Independent batch-part branches (fork/join on auxiliary streams) where
-  // nothing couples the sequences inside the layers: no clamp (its decision
-  // is batch-global), no tensor log, not a KV-cache prefill or a profile,
-  // and every forward part large enough for the tiled GEMMs, whose
-  // per-element arithmetic does not depend on M, so the results are the same
-  // bits as one branch.
+  // A decode step runs as independent batch parts (fork/join on auxiliary
+  // streams).  A forward runs as one branch: its products fill the chip, and
+  // in halves they need more waves of tiles (8 x (512 + 128) positions of the
+  // 768-wide encoder-decoder: 1755 us in two branches, 1627 in one).
   int parts = m->split_parts < B ? m->split_parts : B;
-  // (a decode step's parts run the skinny kernels, so any part size goes)
-  while (!dec && parts > 1 && (B / parts) * S <= 16) --parts;
-  // Models whose projections take the large-tile GEMM (d >= 2048) run a
-  // forward as one branch: a part's products have fewer large tiles than the
-  // chip has CUs (2 x 1024 positions of the 4096-wide decoder: 30.2 ms per
-  // forward as two branches, 28.05 ms as one).
-  if (!dec && d >= 2048) parts = 1;
-  if (prof || dump || work || c.fp16_clamp || c.log_hidden || (c.kv_cache && !dec)) parts = 1;
+  if (!dec || prof || dump || work) parts = 1;
   head_joined = parts > 1 && dec;
   if (parts > 1) {
     // (the graph-broken run splits the same way: its only cut, the guards,
@@ -758,8 +749,7 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
   brk(kCutGuards);   // original program: the source's guards and mask.any() read on the host
 
   // The target's guards and padding predicate: before the decoder (after the
-  // encoder) in one branch, where the graph-broken program reads them; before
-  // the fork when the batch runs as parts.
+  // encoder), where the graph-broken program reads them.
   auto target_prologue = [&](hipStream_t s) {
     if (on())
       launch_prologue(tgt_ids, tgt_mask, B, St, c.vocab, 0, 0, 0, nullptr, 0, nullptr, 0, 0,
@@ -767,30 +757,20 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
     P(GM_K_PROLOGUE, -1, 0.0, 8.0 * Tt);
     brk(kCutGuardsTgt);   // original program: the target's guards and mask.any() read on the host
   };
-  // Sequences [b0, b0 + nb) on stream s: part p's encoder and decoder rows
-  // start at row b0 * S_src of every activation buffer (the decoder rows fit
-  // in the part's encoder rows since S_tgt <= S_src when the batch is split).
-  // Batch parts run as concurrent graph branches when nothing couples them
-  // (not profiled or graph-broken, parts above 16 rows).
-  const int b_half = B / 2;
-  const bool split = m->split_parts > 1 && !prof && !seg && St <= Ss && b_half >= 1 &&
-                     b_half * St > 16;
-  auto part = [&](hipStream_t s, int b0, int nb) {
-  const int Tsp = nb * Ss, Ttp = nb * St;
-  const size_t ro = static_cast<size_t>(b0) * Ss, rt = static_cast<size_t>(b0) * St;
-  char* hh = static_cast<char*>(m->h) + ro * d * m->esz;
-  char* aa = static_cast<char*>(m->a) + ro * d * m->esz;
-  char* qq = static_cast<char*>(m->qkv) + ro * 3 * d * m->esz;
-  char* cc = static_cast<char*>(m->ctx) + ro * d * m->esz;
-  char* ffb = static_cast<char*>(m->f) + ro * ff * m->esz;
-  char* mm = static_cast<char*>(m->mem) + ro * d * m->esz;
-  char* kk = static_cast<char*>(m->kvc) + ro * nd * 2 * d * m->esz;
-  char* qcc = static_cast<char*>(m->qc) + rt * d * m->esz;
-  char* lg = static_cast<char*>(logits) + rt * c.vocab * m->esz;
-  const int32_t* sids = src_ids + ro;
-  const int32_t* tids = tgt_ids + rt;
-  const int32_t* smask = src_mask + ro;
-  const int32_t* tmask = tgt_mask + rt;
+  const int Tsp = Ts, Ttp = Tt, nb = B;
+  char* hh = static_cast<char*>(m->h);
+  char* aa = static_cast<char*>(m->a);
+  char* qq = static_cast<char*>(m->qkv);
+  char* cc = static_cast<char*>(m->ctx);
+  char* ffb = static_cast<char*>(m->f);
+  char* mm = static_cast<char*>(m->mem);
+  char* kk = static_cast<char*>(m->kvc);
+  char* qcc = static_cast<char*>(m->qc);
+  char* lg = static_cast<char*>(logits);
+  const int32_t* sids = src_ids;
+  const int32_t* tids = tgt_ids;
+  const int32_t* smask = src_mask;
+  const int32_t* tmask = tgt_mask;
   RowArgs r{};
   r.dtype = m->dtype;
   r.d = d;
@@ -896,7 +876,7 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
     norm_rows(Tsp, hh, aa, L.ln1_g, L.ln1_b);
     gemm(GM_K_GEMM_QKV, Tsp, aa, d, L.wqkv, 3 * d, kEpiStore, L.bqkv, qq, 3 * d, nullptr);
     attention(GM_K_ATTENTION, Ss, Ss, qkv, 3 * d, qkv + d * m->esz, 3 * d, smask, kPadAny,
-              kKvLenBase + b0, 0);
+              kKvLenBase, 0);
     gemm(GM_K_GEMM_O, Tsp, cc, d, L.wo, d, kEpiResid, L.bo, hh, d, hh);
     block_ffn(Tsp, L);
   }
@@ -909,7 +889,7 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
   // decoder (causal self-attention under the target's padding branch,
   // cross-attention under the source's); its inputs' guards merge into the
   // forward's trap word
-  if (!split) target_prologue(s);
+  target_prologue(s);
   embed(Ttp, St, tids, m->pos_emb);
   for (int l = 0; l < nd; ++l) {
     cur_layer = c.n_layers + l;
@@ -918,30 +898,18 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
     norm_rows(Ttp, hh, aa, L.ln1_g, L.ln1_b);
     gemm(GM_K_GEMM_QKV, Ttp, aa, d, L.wqkv, 3 * d, kEpiStore, L.bqkv, qq, 3 * d, nullptr);
     attention(GM_K_ATTENTION, St, St, qkv, 3 * d, qkv + d * m->esz, 3 * d, tmask, kPadAnyTgt,
-              kKvLenBase + c.max_batch + b0, 1);
+              kKvLenBase + c.max_batch, 1);
     gemm(GM_K_GEMM_O, Ttp, cc, d, L.wo, d, kEpiResid, L.bo, hh, d, hh);
     norm_rows(Ttp, hh, aa, X.lnc_g, X.lnc_b);
     gemm(GM_K_GEMM_XQ, Ttp, aa, d, X.wq, d, kEpiStore, X.bq, qcc, d, nullptr);
     attention(GM_K_XATTN, St, Ss, qcc, d, static_cast<char*>(kk) + static_cast<size_t>(l) * 2 * d * m->esz,
-              nd * 2 * d, smask, kPadAny, kKvLenBase + b0, 0);
+              nd * 2 * d, smask, kPadAny, kKvLenBase, 0);
     gemm(GM_K_GEMM_XO, Ttp, cc, d, X.wo, d, kEpiResid, X.bo, hh, d, hh);
     block_ffn(Ttp, L);
   }
   cur_layer = -1;
   norm_rows(Ttp, hh, aa, m->lnf_g, m->lnf_b);
   gemm(GM_K_GEMM_HEAD, Ttp, aa, d, m->head, c.vocab, kEpiStore, nullptr, lg, c.vocab, nullptr);
-  };
-  if (split) {
-    target_prologue(s);
-    (void)hipEventRecord(m->ev_fork, s);
-    (void)hipStreamWaitEvent(m->aux_stream[0], m->ev_fork, 0);
-    part(s, 0, b_half);
-    part(m->aux_stream[0], b_half, B - b_half);
-    (void)hipEventRecord(m->ev_join[0], m->aux_stream[0]);
-    (void)hipStreamWaitEvent(s, m->ev_join[0], 0);
-  } else {
-    part(s, 0, B);
-  }
   if (on()) launch_emit_effects(m->state, m->fifo, kFifoCap, 0, nullptr, nullptr, 0, 0, B, 1, s);
   P(GM_K_EFFECTS, -1, 0.0, 0.0);
 }

@@ -12,7 +12,7 @@ Calibration: both runs contain the runtime's copy kernel moving a weight of
 known size into library memory (the token embedding: vocab x d_model x 2
 bytes); the largest such dispatch gives the bytes each counter unit stands
 for (FETCH_SIZE of a copy counts half its bytes on this GPU, WRITE_SIZE all
-of them).  The record carries the SHA-256 of gm_gemm.hip so that a stale
+of them).  The record carries the SHA-256 of gm_gemm_tile.h so that a stale
 measurement is not reported after the kernel changes.  Prints a markdown
 table as well.
 """
@@ -106,7 +106,7 @@ def summarize(workload, fetch_dir, write_dir, src):
 def main(argv):
     if len(argv) != 4 or argv[0] not in WORKLOADS:
         raise SystemExit(__doc__)
-    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "gm_gemm.hip")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "gm_gemm_tile.h")
     rec = summarize(argv[0], argv[1], argv[2], src)
     with open(argv[3], "w") as fh:
         json.dump(rec, fh, indent=1)

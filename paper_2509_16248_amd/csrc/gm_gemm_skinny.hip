@@ -1,206 +1,14 @@
-// gm_gemm_skinny.hip -- GEMMs of a few rows (M <= 16: a decode step or a tiny
-// forward): weight-streaming kernels.
+// gm_gemm_skinny.hip -- products of a few rows (M <= 16: a decode step or a
+// tiny forward), optionally with the norm of their input rows.
 #include "gm_gemm_epilogue.h"
 
 namespace gm {
 
-// ------------------------------------------------------------ M <= 16 kernel
-// A decode step multiplies B <= 16 rows by the whole weight: the work is the
-// stream of weight bytes, so the kernel is laid out for HBM, not for MFMA.
-// Workgroup = 8 wavefronts; wavefront w streams R consecutive packed weight
-// rows with 16-byte coalesced loads, every lane covering a slice of K for
-// all MP activation rows (read through L1/L2).  R = 4 (32 rows: a 16-row
-// pair group) for the gated and rotary epilogues, R = 1 (8 rows, four times
-// the workgroups) for the others.  The 64 lanes' partial sums are reduced by
-// a transposing butterfly (each step halves the values a lane carries), the
-// results meet in LDS, and wavefront 0 runs the same epilogue as the tiled
-// kernel.
-template <int NV>
-__device__ __forceinline__ float lane_transpose_sum(float (&v)[NV], int lane, int& index) {
-  index = 0;
-  static_for<0, 6>([&](auto st) {
-    constexpr int o = 32 >> decltype(st)::value;
-    constexpr int n = NV >> decltype(st)::value;
-    if constexpr (n >= 2) {
-      constexpr int half = n / 2;
-      const bool up = (lane & o) != 0;
-#pragma unroll
-      for (int j = 0; j < half; ++j) {
-        const float send = up ? v[j] : v[j + half];
-        const float keep = up ? v[j + half] : v[j];
-        v[j] = keep + __shfl_xor(send, o, 64);
-      }
-      if (up) index += half;
-    } else {
-      v[0] += __shfl_xor(v[0], o, 64);
-    }
-  });
-  return v[0];
-}
-
-template <typename T, int MP, int R>
-__global__ __launch_bounds__(512) void k_gemm_skinny(GemmArgs a) {
-  constexpr int VN = 16 / static_cast<int>(sizeof(T));
-  constexpr int ROWS = 8 * R;               // weight rows per workgroup
-  typedef typename std::conditional<sizeof(T) == 4, f32x4v, u32x4>::type V;
-  __shared__ float res[ROWS][MP + 1];
-  const int n0 = blockIdx.x * ROWS;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const T* W = static_cast<const T*>(a.W);
-  const T* A = static_cast<const T*>(a.A);
-  const T* wrow[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    int n = n0 + wave * R + r;
-    n = n < a.N ? n : a.N - 1;
-    wrow[r] = W + static_cast<long long>(n) * a.ldw;
-  }
-  const T* arow[MP];
-#pragma unroll
-  for (int m = 0; m < MP; ++m) arow[m] = A + static_cast<long long>(m < a.M ? m : a.M - 1) * a.lda;
-  float acc[R * MP];
-#pragma unroll
-  for (int j = 0; j < R * MP; ++j) acc[j] = 0.f;
-#pragma unroll 2
-  for (int k = lane * VN; k < a.K; k += 64 * VN) {
-    float w[R][VN];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const V raw = *reinterpret_cast<const V*>(wrow[r] + k);
-      const T* e = reinterpret_cast<const T*>(&raw);
-#pragma unroll
-      for (int i = 0; i < VN; ++i) w[r][i] = to_f32(e[i]);
-    }
-#pragma unroll
-    for (int m = 0; m < MP; ++m) {
-      const V raw = *reinterpret_cast<const V*>(arow[m] + k);
-      const T* e = reinterpret_cast<const T*>(&raw);
-#pragma unroll
-      for (int i = 0; i < VN; ++i) {
-        const float x = to_f32(e[i]);
-#pragma unroll
-        for (int r = 0; r < R; ++r) acc[r * MP + m] = fmaf(w[r][i], x, acc[r * MP + m]);
-      }
-    }
-  }
-  int idx;
-  const float sum = lane_transpose_sum<R * MP>(acc, lane, idx);
-  // lanes that differ only in their low bits hold the same value
-  if ((lane & (64 / (R * MP) - 1)) == 0) res[wave * R + idx / MP][idx % MP] = sum;
-  __syncthreads();
-  if (wave != 0) return;
-  SiteMax sm;
-  if (R == 4) {
-    // a 16-row pair group: packed rows n0 + 4q + r and n0 + 16 + 4q + r
-    const int m = lane >> 2, q = lane & 3;
-    if (m < MP && m < a.M) {
-      float va[4], vb[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        va[r] = res[4 * q + r][m];
-        vb[r] = res[16 + 4 * q + r][m];
-      }
-      epi_pair<T>(a, m, n0 + 4 * q, va, vb, sm);
-    }
-  } else {
-    // independent columns: 8 rows as two groups of 4; the partner columns
-    // the pair epilogue would also write lie beyond this workgroup's N
-    GemmArgs b = a;
-    b.N = a.N - n0 < ROWS ? a.N : n0 + ROWS;
-    const int m = lane >> 1, q = lane & 1;
-    if (m < MP && m < a.M) {
-      float va[4], vb[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) va[r] = res[4 * q + r][m];
-      epi_pair<T>(b, m, n0 + 4 * q, va, vb, sm);
-    }
-  }
-  site_flush(a, sm);
-}
-
-// Independent-column epilogues on a narrow output: workgroup = 8 weight
-// rows, and the 8 wavefronts split K instead of the rows, each covering all
-// 8 rows for its K slice, so every lane's loads (8 weight and MP activation
-// vectors per step) leave together and a short K needs a single round trip
-// to memory.  Lane partials are reduced by the transposing butterfly, the 8
-// wavefronts' sums are added in LDS.
-template <typename T, int MP>
-__global__ __launch_bounds__(512) void k_gemm_skinny_ks(GemmArgs a) {
-  constexpr int VN = 16 / static_cast<int>(sizeof(T));
-  constexpr int R = 8;
-  typedef typename std::conditional<sizeof(T) == 4, f32x4v, u32x4>::type V;
-  __shared__ float part[8][R * MP];
-  __shared__ float res[R][MP + 1];
-  const int n0 = blockIdx.x * R;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const T* W = static_cast<const T*>(a.W);
-  const T* A = static_cast<const T*>(a.A);
-  // this wavefront's K slice, a multiple of VN
-  const int per = ((a.K + 8 * VN - 1) / (8 * VN)) * VN;
-  const int kb = wave * per, ke = min(a.K, kb + per);
-  const T* wrow[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    int n = n0 + r;
-    n = n < a.N ? n : a.N - 1;
-    wrow[r] = W + static_cast<long long>(n) * a.ldw;
-  }
-  const T* arow[MP];
-#pragma unroll
-  for (int m = 0; m < MP; ++m) arow[m] = A + static_cast<long long>(m < a.M ? m : a.M - 1) * a.lda;
-  float acc[R * MP];
-#pragma unroll
-  for (int j = 0; j < R * MP; ++j) acc[j] = 0.f;
-  for (int k = kb + lane * VN; k < ke; k += 64 * VN) {
-    V wv[R], av[MP];
-#pragma unroll
-    for (int r = 0; r < R; ++r) wv[r] = *reinterpret_cast<const V*>(wrow[r] + k);
-#pragma unroll
-    for (int m = 0; m < MP; ++m) av[m] = *reinterpret_cast<const V*>(arow[m] + k);
-#pragma unroll
-    for (int m = 0; m < MP; ++m) {
-      const T* ae = reinterpret_cast<const T*>(&av[m]);
-#pragma unroll
-      for (int i = 0; i < VN; ++i) {
-        const float x = to_f32(ae[i]);
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-          acc[r * MP + m] = fmaf(to_f32(reinterpret_cast<const T*>(&wv[r])[i]), x, acc[r * MP + m]);
-      }
-    }
-  }
-  int idx;
-  const float sum = lane_transpose_sum<R * MP>(acc, lane, idx);
-  if ((lane & (64 / (R * MP) - 1)) == 0) part[wave][idx] = sum;
-  __syncthreads();
-  if (threadIdx.x < R * MP) {
-    float t = 0.f;
-#pragma unroll
-    for (int w2 = 0; w2 < 8; ++w2) t += part[w2][threadIdx.x];
-    res[threadIdx.x / MP][threadIdx.x % MP] = t;
-  }
-  __syncthreads();
-  if (wave != 0) return;
-  SiteMax sm;
-  GemmArgs b = a;
-  b.N = a.N - n0 < R ? a.N : n0 + R;
-  const int m = lane >> 1, q = lane & 1;
-  if (m < MP && m < a.M) {
-    float va[4], vb[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int r = 0; r < 4; ++r) va[r] = res[4 * q + r][m];
-    epi_pair<T>(b, m, n0 + 4 * q, va, vb, sm);
-  }
-  site_flush(a, sm);
-}
-
-// A few rows (M <= 16) against a wide plain output (the LM head of a
-// decode step): the 2 M N K multiply-adds on the matrix cores instead of
-// the VALU.  Each wavefront computes 16 output columns for every row with
-// v_mfma_f32_16x16x32 (16 weight rows as the A operand, the activation rows
-// padded to 16 as the B operand; lane l supplies row l % 16 and k
-// 8 (l / 16) .. + 7 of each 32-wide k step), 8 k steps of loads in flight,
-// and ends with columns 4 (l / 16) .. + 3 of activation row l % 16.
+// v_mfma_f32_16x16x32 of 16 weight rows (A operand) and up to 16 activation
+// rows (B operand): lane l supplies 16 bytes of row l % 16 at k-chunk l / 16 of
+// a step, and ends with output columns 4 (l / 16) .. + 3 of activation row
+// l % 16.  fp32: four v_mfma_f32_16x16x4 per step, MFMA r taking element r of
+// every lane's four (the order of the sum over k is free).
 template <typename T> struct Mfma16;
 template <> struct Mfma16<bf16_t> {
   typedef bf16x8 vec;
@@ -214,85 +22,259 @@ template <> struct Mfma16<f16_t> {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
 };
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_gemm_skinny_mfma(GemmArgs a) {
-  typedef typename Mfma16<T>::vec vec;
-  constexpr int U = 8;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n0 = (blockIdx.x * 4 + wave) * 16;
-  if (n0 >= a.N) return;                     // no barrier in this kernel
-  const int l16 = lane & 15, kg = lane >> 4;
-  const int n = n0 + l16 < a.N ? n0 + l16 : a.N - 1;
-  const int m = l16 < a.M ? l16 : a.M - 1;
-  const T* wp = static_cast<const T*>(a.W) + static_cast<long long>(n) * a.ldw + 8 * kg;
-  const T* xp = static_cast<const T*>(a.A) + static_cast<long long>(m) * a.lda + 8 * kg;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  int k = 0;
-  for (; k + 32 * U <= a.K; k += 32 * U) {
-    vec wf[U], xf[U];
+template <> struct Mfma16<float> {
+  typedef f32x4 vec;
+  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      wf[u] = *reinterpret_cast<const vec*>(wp + k + 32 * u);
-      xf[u] = *reinterpret_cast<const vec*>(xp + k + 32 * u);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) acc = Mfma16<T>::run(wf[u], xf[u], acc);
+    for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], c, 0, 0, 0);
+    return c;
   }
-  for (; k < a.K; k += 32)
-    acc = Mfma16<T>::run(*reinterpret_cast<const vec*>(wp + k), *reinterpret_cast<const vec*>(xp + k),
-                         acc);
+};
+
+constexpr int kRowsWaves = 8;
+
+// Rows of x normalised into LDS (pitch elements apart), one wavefront per
+// row: the arithmetic of the row kernel, so the same bits.
+template <typename T, int MAXV>
+__device__ __forceinline__ void norm_to_lds(const GemmArgs& a, T* lds, int pitch, int wave, int lane) {
+  typedef typename std::conditional<sizeof(T) == 4, f32x4v, u32x4>::type V;
+  constexpr int VN = 16 / static_cast<int>(sizeof(T));
+  const int d = a.K, nvec = d / VN;
+  const T* g = static_cast<const T*>(a.norm_g);
+  const T* bb = static_cast<const T*>(a.norm_b);
+  for (int row = wave; row < a.M; row += kRowsWaves) {
+    const T* x = static_cast<const T*>(a.A) + static_cast<long long>(row) * a.lda;
+    V raw[MAXV], graw[MAXV], braw[MAXV];
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) {
+      const int c = lane + 64 * j;
+      if (c < nvec) {
+        raw[j] = *reinterpret_cast<const V*>(x + c * VN);
+        graw[j] = *reinterpret_cast<const V*>(g + c * VN);
+        if (bb) braw[j] = *reinterpret_cast<const V*>(bb + c * VN);
+      }
+    }
+    float s1 = 0.f;
+    if (a.norm == 0) {
+#pragma unroll
+      for (int j = 0; j < MAXV; ++j)
+        if (lane + 64 * j < nvec)
+#pragma unroll
+          for (int i = 0; i < VN; ++i) s1 += to_f32(reinterpret_cast<const T*>(&raw[j])[i]);
+      s1 = wave_sum(s1);
+    }
+    const float mean = a.norm == 0 ? s1 / d : 0.f;
+    float s2 = 0.f;
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j)
+      if (lane + 64 * j < nvec)
+#pragma unroll
+        for (int i = 0; i < VN; ++i) {
+          const float c = to_f32(reinterpret_cast<const T*>(&raw[j])[i]) - mean;
+          s2 += c * c;
+        }
+    s2 = wave_sum(s2);
+    const float rstd = 1.0f / sqrtf(s2 / d + a.norm_eps);
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) {
+      const int c = lane + 64 * j;
+      if (c < nvec) {
+        V w;
+        T* we = reinterpret_cast<T*>(&w);
+#pragma unroll
+        for (int i = 0; i < VN; ++i) {
+          const float bv = bb ? to_f32(reinterpret_cast<const T*>(&braw[j])[i]) : 0.f;
+          we[i] = from_f32<T>((to_f32(reinterpret_cast<const T*>(&raw[j])[i]) - mean) * rstd *
+                                  to_f32(reinterpret_cast<const T*>(&graw[j])[i]) + bv);
+        }
+        *reinterpret_cast<V*>(lds + row * pitch + c * VN) = w;
+      }
+    }
+  }
+}
+
+// How a product of a few rows takes the norm of its input.
+enum RowsNorm : int {
+  kRowsPlain = 0,   // it does not
+  kRowsLds = 1,     // rows normalised into LDS first, MAXV = 2 vectors per lane
+  kRowsScaled = 2,  // RMSNorm: rows times gain are multiplied, the sums scaled
+};
+
+// The work of a few rows is the stream of weight bytes, and where those are
+// few (a 768-wide model) the latency of one launch.  A workgroup computes CT
+// groups of 16 output columns for every row; its 8 wavefronts take pairs of
+// steps of K in turn (two steps: 128 bytes, a cache line, of each weight row;
+// one step each apart: 25.8 against 20.6 us on 4096 x 11008), with two pairs in
+// flight per wavefront (more leave fewer wavefronts room: 42 -> 51 us on 22016
+// x 4096), and the wavefronts' sums meet in LDS.
+// The norm of the input rows costs no launch of its own (3.8 - 5.2 us):
+//  - up to 128 vectors per row it is computed into LDS while the first weights
+//    are on their way (8 x 2304 x 768: 3.7 -> 4.7 us; for longer rows the wait
+//    costs more than the launch: 1 x 22016 x 4096 42 -> 57 us);
+//  - a longer RMSNorm does not come before the product at all: its gain is
+//    multiplied into the rows (one rounding, as before), every wavefront sums
+//    the squares of the elements it reads, and the finished sums are scaled.
+// Against kernels of vector instructions that streamed whole weight rows:
+// 8 x 22016 x 4096 87 -> 46 us, 8 x 2304 x 768 7.0 -> 3.5, 1 x 12288 x 4096 31 -> 27.
+template <typename T, int CT, int NORM>
+__global__ __launch_bounds__(64 * kRowsWaves) void k_gemm_rows(GemmArgs a) {
+  typedef typename Mfma16<T>::vec vec;
+  constexpr int VN = 16 / static_cast<int>(sizeof(T));
+  constexpr int KC = 4 * VN;                       // k per step
+  constexpr int U = 2;                             // steps per batch of loads
+  extern __shared__ __attribute__((aligned(16))) char dyn[];
+  __shared__ f32x4 red[kRowsWaves][CT][64];
+  __shared__ float red_ss[kRowsWaves][16];
+  T* xl = reinterpret_cast<T*>(dyn);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, kg = lane >> 4;
+  const int n0 = blockIdx.x * 16 * CT;
+  const T* wp[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    int n = n0 + 16 * c + l16;
+    n = n < a.N ? n : a.N - 1;
+    wp[c] = static_cast<const T*>(a.W) + static_cast<long long>(n) * a.ldw + kg * VN;
+  }
+  const int m = l16 < a.M ? l16 : a.M - 1;
+  const int pitch = a.K + VN;                      // 16 rows in distinct banks
+  const T* xp = NORM == kRowsLds ? xl + m * pitch + kg * VN
+                                 : static_cast<const T*>(a.A) + static_cast<long long>(m) * a.lda + kg * VN;
+  const T* gp = static_cast<const T*>(a.norm_g) + kg * VN;
+  const int steps = a.K / KC;
+  f32x4 acc[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float ss = 0.f;                                  // sum of squares of this lane's elements
+  vec w[2][CT][U], x[2][U], gn[2][U];
+  auto fetch = [&](auto set, int s0) {             // steps s0 .. s0 + U - 1
+    static_for<0, U>([&](auto u) {
+      const int s = s0 + u;
+      if (s < steps) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) w[set][c][u] = *reinterpret_cast<const vec*>(wp[c] + s * KC);
+        if constexpr (NORM != kRowsLds) x[set][u] = *reinterpret_cast<const vec*>(xp + s * KC);
+        if constexpr (NORM == kRowsScaled) gn[set][u] = *reinterpret_cast<const vec*>(gp + s * KC);
+      }
+    });
+  };
+  auto multiply = [&](auto set, int s0) {
+    static_for<0, U>([&](auto u) {
+      const int s = s0 + u;
+      if (s < steps) {
+        if constexpr (NORM == kRowsLds) x[set][u] = *reinterpret_cast<const vec*>(xp + s * KC);
+        if constexpr (NORM == kRowsScaled) {
+          T* xe = reinterpret_cast<T*>(&x[set][u]);
+          const T* ge = reinterpret_cast<const T*>(&gn[set][u]);
+#pragma unroll
+          for (int i = 0; i < VN; ++i) {
+            const float v = to_f32(xe[i]);
+            ss += v * v;
+            xe[i] = from_f32<T>(v * to_f32(ge[i]));
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[c] = Mfma16<T>::run(w[set][c][u], x[set][u], acc[c]);
+      }
+    });
+  };
+  constexpr int B = kRowsWaves * U;                // steps per batch over the workgroup
+  std::integral_constant<int, 0> s0;
+  std::integral_constant<int, 1> s1;
+  fetch(s0, wave * U);
+  fetch(s1, wave * U + B);
+  if constexpr (NORM == kRowsLds) {
+    norm_to_lds<T, 2>(a, xl, pitch, wave, lane);
+    __syncthreads();
+  }
+  for (int s = wave * U; s < steps; s += 2 * B) {
+    multiply(s0, s);
+    fetch(s0, s + 2 * B);
+    multiply(s1, s + B);
+    fetch(s1, s + 3 * B);
+  }
+#pragma unroll
+  for (int c = 0; c < CT; ++c) red[wave][c][lane] = acc[c];
+  if constexpr (NORM == kRowsScaled) {
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    if (lane < 16) red_ss[wave][lane] = ss;
+  }
+  __syncthreads();
+  constexpr int PAIRS = CT > 1 ? CT / 2 : 1;
+  if (wave >= PAIRS) return;
+  float scale = 1.f;
+  if constexpr (NORM == kRowsScaled) {
+    float t = 0.f;
+#pragma unroll
+    for (int v = 0; v < kRowsWaves; ++v) t += red_ss[v][l16];
+    scale = 1.0f / sqrtf(t / a.K + a.norm_eps);
+  }
+  auto total = [&](int c) {
+    f32x4 t = red[0][c][lane];
+#pragma unroll
+    for (int v = 1; v < kRowsWaves; ++v) t += red[v][c][lane];
+    if constexpr (NORM == kRowsScaled) t *= scale;
+    return t;
+  };
   SiteMax sm;
-  GemmArgs b = a;
-  b.N = a.N - n0 < 16 ? a.N : n0 + 16;       // the pair columns (+16) lie beyond this wavefront's
-  const float va[4] = {acc[0], acc[1], acc[2], acc[3]};
-  const float vb[4] = {0.f, 0.f, 0.f, 0.f};
-  epi_pair<T>(b, l16, n0 + 4 * kg, va, vb, sm);
+  const f32x4 ta = total(CT > 1 ? 2 * wave : 0);
+  const float va[4] = {ta[0], ta[1], ta[2], ta[3]};
+  const int nA = n0 + 32 * wave + 4 * kg;
+  if constexpr (CT > 1) {
+    const f32x4 tb = total(2 * wave + 1);
+    const float vb[4] = {tb[0], tb[1], tb[2], tb[3]};
+    epi_pair<T>(a, l16, nA, va, vb, sm);
+  } else {
+    // the partner columns the pair epilogue would also write lie beyond this
+    // workgroup's
+    GemmArgs b = a;
+    b.N = a.N - n0 < 16 ? a.N : n0 + 16;
+    const float vb[4] = {0.f, 0.f, 0.f, 0.f};
+    epi_pair<T>(b, l16, nA, va, vb, sm);
+  }
   site_flush(a, sm);
 }
 
-template <typename T>
-static void skinny_ks(const GemmArgs& a, hipStream_t s) {
-  const dim3 grid((a.N + 7) / 8), block(512);
-  if (a.M <= 1) hipLaunchKernelGGL((k_gemm_skinny_ks<T, 1>), grid, block, 0, s, a);
-  else if (a.M <= 2) hipLaunchKernelGGL((k_gemm_skinny_ks<T, 2>), grid, block, 0, s, a);
-  else if (a.M <= 4) hipLaunchKernelGGL((k_gemm_skinny_ks<T, 4>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((k_gemm_skinny_ks<T, 8>), grid, block, 0, s, a);
+static RowsNorm rows_norm(int dtype, int norm, int d) {
+  const int es = dtype == kF32 ? 4 : 2;
+  if (d * es <= 2 * 64 * 16) return kRowsLds;      // two vectors per lane; 33 KB of LDS at 16 rows
+  // (a row times the gain must not leave the range: not in fp16)
+  return norm == 1 && dtype != kF16 ? kRowsScaled : kRowsPlain;
 }
 
-template <typename T, int R>
-static void skinny_r(const GemmArgs& a, hipStream_t s) {
-  const dim3 grid((a.N + 8 * R - 1) / (8 * R)), block(512);
-  if (a.M <= 1) hipLaunchKernelGGL((k_gemm_skinny<T, 1, R>), grid, block, 0, s, a);
-  else if (a.M <= 2) hipLaunchKernelGGL((k_gemm_skinny<T, 2, R>), grid, block, 0, s, a);
-  else if (a.M <= 4) hipLaunchKernelGGL((k_gemm_skinny<T, 4, R>), grid, block, 0, s, a);
-  else if (a.M <= 8) hipLaunchKernelGGL((k_gemm_skinny<T, 8, R>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((k_gemm_skinny<T, 16, R>), grid, block, 0, s, a);
+bool gemm_takes_norm(int dtype, int M, int d, int norm) {
+  return M <= 16 && rows_norm(dtype, norm, d) != kRowsPlain;
 }
 
-template <typename T>
-static void skinny_t(const GemmArgs& a, hipStream_t s) {
-  // the gated and rotary epilogues combine packed rows 16 apart; a wide
-  // output (the head) has workgroups enough with 32 rows each, and four rows
-  // per wavefront reuse every activation load four times
-  // a wide plain output (the head) in 16-bit on the matrix cores
-  if constexpr (sizeof(T) == 2) {
-    if (a.epi == kEpiStore && !a.bias && a.site < 0 && !a.kc && a.N >= 8192 && a.K % 32 == 0) {
-      hipLaunchKernelGGL((k_gemm_skinny_mfma<T>), dim3((a.N + 63) / 64), dim3(256), 0, s, a);
-      return;
-    }
-  }
-  if (a.epi == kEpiGatedGelu || a.epi == kEpiGatedSilu || a.epi == kEpiRope || a.N >= 8192)
-    skinny_r<T, 4>(a, s);
-  else if (a.M <= 8 && a.N < 2048)     // few row groups: split K across the wavefronts
-    skinny_ks<T>(a, s);
+template <typename T, int CT>
+static void rows_ct(const GemmArgs& a, hipStream_t s) {
+  constexpr int ES = static_cast<int>(sizeof(T));
+  const dim3 grid((a.N + 16 * CT - 1) / (16 * CT)), block(64 * kRowsWaves);
+  if (a.norm < 0)
+    hipLaunchKernelGGL((k_gemm_rows<T, CT, kRowsPlain>), grid, block, 0, s, a);
+  else if (rows_norm(a.dtype, a.norm, a.K) == kRowsLds)
+    hipLaunchKernelGGL((k_gemm_rows<T, CT, kRowsLds>), grid, block, a.M * (a.K * ES + 16), s, a);
   else
-    skinny_r<T, 1>(a, s);
+    hipLaunchKernelGGL((k_gemm_rows<T, CT, kRowsScaled>), grid, block, 0, s, a);
 }
+
+template <typename T>
+static void rows_t(const GemmArgs& a, hipStream_t s) {
+  // the gated and rotary epilogues combine packed columns 16 apart; a wide
+  // output has workgroups enough with 32 columns each and reads the input
+  // rows half as often
+  if (a.epi == kEpiGatedGelu || a.epi == kEpiGatedSilu || a.epi == kEpiRope || a.N >= 8192)
+    rows_ct<T, 2>(a, s);
+  else
+    rows_ct<T, 1>(a, s);
+}
+
 void gemm_skinny(const GemmArgs& a, hipStream_t s) {
-  if (a.dtype == kF32) skinny_t<float>(a, s);
-  else if (a.dtype == kBF16) skinny_t<bf16_t>(a, s);
-  else skinny_t<f16_t>(a, s);
+  if (a.dtype == kF32) rows_t<float>(a, s);
+  else if (a.dtype == kBF16) rows_t<bf16_t>(a, s);
+  else rows_t<f16_t>(a, s);
 }
 
 }  // namespace gm

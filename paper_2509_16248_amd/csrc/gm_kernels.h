@@ -41,10 +41,15 @@ struct GemmArgs {
   // ([B][H][kv_max_seq][head_dim]) and the position marked valid, unless the
   // step trapped
   void* kc; void* vc; uint8_t* kv_valid; int kv_max_seq; int heads;
+  // few-row products only (gemm_takes_norm): A is normalised first
+  // (-1: no, 0 LayerNorm, 1 RMSNorm over its K columns)
+  int norm; const void* norm_g; const void* norm_b; float norm_eps;
 };
 // M <= 16 rows (a decode step, or a tiny forward) runs on a weight-streaming
 // kernel; larger M on the tiled MFMA kernel.
 void launch_gemm(const GemmArgs& a, hipStream_t s);
+// Whether launch_gemm accepts GemmArgs::norm = norm for M rows of d columns.
+bool gemm_takes_norm(int dtype, int M, int d, int norm);
 
 struct AttnArgs {
   int dtype;

@@ -114,13 +114,6 @@ struct gm_model {
   float *rope_cos = nullptr, *rope_sin = nullptr;
   void* fifo = nullptr;
   hipStream_t cap_stream = nullptr;
-  // further batch-part branches of a forward: their streams and the
-  // fork/join events (the branches are independent, so the GPU overlaps one
-  // part's latency-bound kernels with another part's GEMMs)
-  static constexpr int kMaxParts = 4;
-  hipStream_t aux_stream[kMaxParts - 1] = {};
-  hipEvent_t ev_fork = nullptr, ev_join[kMaxParts - 1] = {};
-  int split_parts = 2;
   std::vector<GraphEntry> graphs;
   gm_stats stats;
   int exec_mode = GM_EXEC_GRAPH;
@@ -444,20 +437,13 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   P(GM_K_EMBED, -1, 0.0, static_cast<double>(T) * d * es * (c.pos == GM_POS_LEARNED ? 3 : 2));
   r.ids = nullptr;
 
-  // a decode step's head runs once over the whole batch after the join (one
-  // pass over the head's weights instead of one per part)
-  bool head_joined = false;
-  // The layers and the head over sequences [b0, b0 + nb) on stream s.
-  auto layers_and_head = [&](hipStream_t s, int b0, int nb) {
-  const int T = nb * S;
-  const size_t ro = static_cast<size_t>(b0) * S;   // first row of this part
-  char* hh = static_cast<char*>(wk.h) + ro * d * m->esz;
-  char* aa = static_cast<char*>(wk.a) + ro * d * m->esz;
-  char* qq = static_cast<char*>(wk.qkv) + ro * 3 * d * m->esz;
-  char* cc = static_cast<char*>(wk.ctx) + ro * d * m->esz;
-  char* ffb = static_cast<char*>(wk.f) + ro * ff * m->esz;
-  char* tt = wk.tmp ? static_cast<char*>(wk.tmp) + ro * d * m->esz : nullptr;
-  char* lg = static_cast<char*>(logits) + ro * c.vocab * m->esz;
+  const int nb = B;
+  char* hh = static_cast<char*>(wk.h);
+  char* aa = static_cast<char*>(wk.a);
+  char* qq = static_cast<char*>(wk.qkv);
+  char* cc = static_cast<char*>(wk.ctx);
+  char* ffb = static_cast<char*>(wk.f);
+  char* tt = static_cast<char*>(wk.tmp);
   auto norm_rows = [&](void* x, void* out, const void* g, const void* b, int site) {
     RowArgs q = r;
     q.rows = T;
@@ -477,23 +463,31 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   ga.state = m->state;
   ga.site = -1;
   ga.seq = S;
-  ga.pos = dec ? m->dpos + b0 : nullptr;
+  ga.pos = dec ? m->dpos : nullptr;
   ga.head_dim = hd;
   ga.d_model = d;
   ga.rope_cos = m->rope_cos;
   ga.rope_sin = m->rope_sin;
   ga.rope_rows = c.rope_capacity > 0 ? c.rope_capacity : 1;
   ga.rope_set_stride = c.rope_scaling ? c.rope_capacity * (hd / 2) : 0;
+  ga.norm = -1;
+  struct Norm {
+    const void *g, *b;
+  };
   auto gemm = [&](int kind, const void* A, int K, const void* W, int N, int epi, const void* bias,
-                  void* out, int ldo, const void* resid, int site) {
+                  void* out, int ldo, const void* resid, int site, const Norm* norm = nullptr) {
     GemmArgs q = ga;
+    if (norm) {
+      q.norm = normk;
+      q.norm_g = norm->g;
+      q.norm_b = norm->b;
+      q.norm_eps = c.norm_eps;
+    }
     if (dec && kind == GM_K_GEMM_QKV) {
       // a decode step stores this layer's new k and v from the epilogue
-      // this part's sequences in the cache ([B][H][max_seq][hd])
-      const size_t co = static_cast<size_t>(b0) * c.n_heads * c.max_seq * hd * m->esz;
-      q.kc = static_cast<char*>(m->kc[cur_layer]) + co;
-      q.vc = static_cast<char*>(m->vc[cur_layer]) + co;
-      q.kv_valid = m->kv_valid + static_cast<size_t>(b0) * c.max_seq;
+      q.kc = m->kc[cur_layer];
+      q.vc = m->vc[cur_layer];
+      q.kv_valid = m->kv_valid;
       q.kv_max_seq = c.max_seq;
       q.heads = c.n_heads;
     }
@@ -531,10 +525,10 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   at.v = static_cast<const char*>(qq) + 2 * d * m->esz;
   at.ldkv = 3 * d;
   at.ctx = cc;
-  at.mask = mask ? mask + static_cast<size_t>(b0) * S : nullptr;
+  at.mask = mask;
   at.state = m->state;
   at.pad_slot = kPadAny;
-  at.kvlen_base = kKvLenBase + b0;
+  at.kvlen_base = kKvLenBase;
   at.causal = c.causal;
   at.scale = 1.0f / sqrtf(static_cast<float>(hd));
 
@@ -565,25 +559,24 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   da.hd = hd;
   da.d = d;
   da.qkv = qq;
-  da.valid = m->kv_valid + static_cast<size_t>(b0) * c.max_seq;
+  da.valid = m->kv_valid;
   da.max_seq = c.max_seq;
-  da.pos = m->dpos + b0;
+  da.pos = m->dpos;
   da.ctx = cc;
   da.part = m->dpart;
   {
-    // split the keys only when there are fewer than ~100 (sequence, head)
-    // pairs to spread over the GPU (a split costs a merge launch); the
-    // pairs are counted over the whole batch, as the batch parts run
-    // concurrently (measured: splitting 8 x 12 heads further is no faster);
-    // chunks are a multiple of 64 keys
+    // Split the keys only when there are fewer than ~100 (sequence, head)
+    // pairs to spread over the GPU and the cache is longer than four round
+    // trips of a workgroup's loads (keys_per_trip): a split costs a merge
+    // launch of 4.8 us, a round trip about 1.5 (measured: splitting 8 x 12
+    // heads further is no faster); chunks are a multiple of 64 keys.
+    const int keys_per_trip = static_cast<int>(65536 / (hd * m->esz));
     int want = (96 + B * c.n_heads - 1) / (B * c.n_heads);
     want = want < m->dec_nsplit ? want : m->dec_nsplit;
-    want = want > 1 ? want : 1;
+    want = want > 1 && c.max_seq > 4 * keys_per_trip ? want : 1;
     da.chunk = 64 * ((c.max_seq + 64 * want - 1) / (64 * want));
     da.nsplit = (c.max_seq + da.chunk - 1) / da.chunk;
   }
-  // this part's rows of the split-key workspace ([B][H][nsplit][hd + 2])
-  if (m->dpart) da.part = m->dpart + static_cast<size_t>(b0) * c.n_heads * da.nsplit * (hd + 2);
   da.scale = at.scale;
   auto attention = [&]() {
     if (c.kv_cache && !dec) {
@@ -595,9 +588,8 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
       P(GM_K_KV_STORE, cur_layer, 0.0, 4.0 * T * d * es);
     }
     if (dec) {
-      const size_t co = static_cast<size_t>(b0) * c.n_heads * c.max_seq * hd * m->esz;
-      da.kc = static_cast<char*>(m->kc[cur_layer]) + co;
-      da.vc = static_cast<char*>(m->vc[cur_layer]) + co;
+      da.kc = m->kc[cur_layer];
+      da.vc = m->vc[cur_layer];
       launch_decode_attention(da, s);
       const double keys = static_cast<double>(B) * c.max_seq;   // upper bound: full cache
       P(GM_K_ATTENTION, cur_layer, 4.0 * hd * keys * c.n_heads, es * 2.0 * keys * d);
@@ -605,6 +597,19 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
     }
     if (on()) launch_attention(at, s);
     P(GM_K_ATTENTION, cur_layer, attn_flops, attn_bytes);
+  };
+  // A pre-norm and the product that reads it: one launch for a few rows, two
+  // where the clamp select or a debug copy needs the normalised rows stored.
+  auto norm_gemm = [&](int kind, const void* g, const void* b, int prior_site, const void* W, int N,
+                       int epi, const void* bias, void* out, int ldo) {
+    if (prior_site < 0 && !dump && gemm_takes_norm(m->dtype, T, d, normk)) {
+      const Norm n{g, b};
+      gemm(kind, hh, d, W, N, epi, bias, out, ldo, nullptr, -1, &n);
+      return;
+    }
+    norm_rows(hh, aa, g, b, prior_site);
+    if (dump && kind != GM_K_GEMM_HEAD) dump->copy(cur_layer, kind == GM_K_GEMM_QKV ? 0 : 4, aa, s);
+    gemm(kind, aa, d, W, N, epi, bias, out, ldo, nullptr, -1);
   };
   int prev_site = -1;
   for (int l = 0; l < c.n_layers; ++l) {
@@ -615,17 +620,14 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
       auto D = [&](int which, const void* src) {
         if (dump) dump->copy(l, which, src, s);
       };
-      norm_rows(hh, aa, L.ln1_g, L.ln1_b, prev_site);
-      D(0, aa);
-      gemm(GM_K_GEMM_QKV, aa, d, L.wqkv, 3 * d, qkv_epi, L.bqkv, qq, 3 * d, nullptr, -1);
+      norm_gemm(GM_K_GEMM_QKV, L.ln1_g, L.ln1_b, prev_site, L.wqkv, 3 * d, qkv_epi, L.bqkv, qq,
+                3 * d);
       D(1, qq);
       attention();
       D(2, cc);
       gemm(GM_K_GEMM_O, cc, d, L.wo, d, kEpiResid, L.bo, hh, d, hh, s0);
       D(3, hh);
-      norm_rows(hh, aa, L.ln2_g, L.ln2_b, s0);
-      D(4, aa);
-      gemm(GM_K_GEMM_UP, aa, d, L.w1, up_n, up_epi, L.b1, ffb, ff, nullptr, -1);
+      norm_gemm(GM_K_GEMM_UP, L.ln2_g, L.ln2_b, s0, L.w1, up_n, up_epi, L.b1, ffb, ff);
       D(5, ffb);
       gemm(GM_K_GEMM_DOWN, ffb, ff, L.w2, d, kEpiResid, L.b2, hh, d, hh, s1);
       D(6, hh);
@@ -650,65 +652,14 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
     }
   }
   cur_layer = -1;
-  const void* z = hh;
-  if (pre) {
-    norm_rows(hh, aa, m->lnf_g, m->lnf_b, prev_site);
-    z = aa;
-  }
-  if (head_joined) return;
-  gemm(GM_K_GEMM_HEAD, z, d, m->head, c.vocab, kEpiStore, nullptr, lg, c.vocab, nullptr, -1);
+  if (pre)
+    norm_gemm(GM_K_GEMM_HEAD, m->lnf_g, m->lnf_b, prev_site, m->head, c.vocab, kEpiStore, nullptr,
+              logits, c.vocab);
+  else
+    gemm(GM_K_GEMM_HEAD, hh, d, m->head, c.vocab, kEpiStore, nullptr, logits, c.vocab, nullptr, -1);
   if (dec && dec->next) {
-    launch_argmax(lg, m->dtype, nb, c.vocab, dec->next + b0, s);
+    launch_argmax(logits, m->dtype, B, c.vocab, dec->next, s);
     P(GM_K_ARGMAX, -1, 0.0, es * B * static_cast<double>(c.vocab));
-  }
-  };
-  // A decode step runs as independent batch parts (fork/join on auxiliary
-  // streams).  A forward runs as one branch: its products fill the chip, and
-  // in halves they need more waves of tiles (8 x (512 + 128) positions of the
-  // 768-wide encoder-decoder: 1755 us in two branches, 1627 in one).
-  int parts = m->split_parts < B ? m->split_parts : B;
-  if (!dec || prof || dump || work) parts = 1;
-  head_joined = parts > 1 && dec;
-  if (parts > 1) {
-    // (the graph-broken run splits the same way: its only cut, the guards,
-    // lies before the fork, and the fork and join go into the segment that
-    // holds the layers)
-    if (on()) {
-      (void)hipEventRecord(m->ev_fork, s);
-      for (int i = 0; i + 1 < parts; ++i) (void)hipStreamWaitEvent(m->aux_stream[i], m->ev_fork, 0);
-    }
-    for (int i = 0; i < parts; ++i) {
-      const int b0 = B * i / parts, b1 = B * (i + 1) / parts;
-      layers_and_head(i == 0 ? s : m->aux_stream[i - 1], b0, b1 - b0);
-    }
-    if (on())
-      for (int i = 0; i + 1 < parts; ++i) {
-        (void)hipEventRecord(m->ev_join[i], m->aux_stream[i]);
-        (void)hipStreamWaitEvent(s, m->ev_join[i], 0);
-      }
-    if (head_joined) {
-      GemmArgs q{};
-      q.dtype = m->dtype;
-      q.M = B;
-      q.N = c.vocab;
-      q.K = d;
-      q.A = pre ? wk.a : wk.h;   // the final norm's output, or the stream itself
-      q.lda = d;
-      q.W = m->head;
-      q.ldw = d;
-      q.epi = kEpiStore;
-      q.out = logits;
-      q.ldo = c.vocab;
-      q.state = m->state;
-      q.site = -1;
-      q.seq = S;
-      q.head_dim = hd;
-      q.d_model = d;
-      launch_gemm(q, s);
-      if (dec->next) launch_argmax(logits, m->dtype, B, c.vocab, dec->next, s);
-    }
-  } else {
-    layers_and_head(s, 0, B);
   }
   if (c.kv_cache && on()) launch_seqlen_update(m->seqlen, m->dpos, m->state, B, dec ? 1 : 0, s);
   if (on())
@@ -805,6 +756,7 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
   auto gemm = [&](int kind, int M, const void* A, int K, const void* W, int N, int epi,
                   const void* bias, void* out, int ldo, const void* resid) {
     GemmArgs q{};
+    q.norm = -1;
     q.dtype = m->dtype;
     q.M = M;
     q.state = m->state;
@@ -991,11 +943,6 @@ void gm_model_destroy(gm_model* m) {
   for (auto& f : m->frags)
     for (hipGraphExec_t e : f.execs) hipGraphExecDestroy(e);
   if (m->cap_stream) hipStreamDestroy(m->cap_stream);
-  for (int i = 0; i < gm_model::kMaxParts - 1; ++i) {
-    if (m->aux_stream[i]) hipStreamDestroy(m->aux_stream[i]);
-    if (m->ev_join[i]) hipEventDestroy(m->ev_join[i]);
-  }
-  if (m->ev_fork) hipEventDestroy(m->ev_fork);
   for (void* p : m->allocs) hipFree(p);
   delete m;
 }
@@ -1263,17 +1210,7 @@ int gm_model_create(const gm_config* cfg, const gm_weights* w, gm_model** out) {
     if (e != hipSuccess) return fail(hip_fail(e, "rope init"));
   }
   e = hipStreamCreateWithFlags(&m->cap_stream, hipStreamNonBlocking);
-  for (int i = 0; e == hipSuccess && i < gm_model::kMaxParts - 1; ++i)
-    e = hipStreamCreateWithFlags(&m->aux_stream[i], hipStreamNonBlocking);
   if (e != hipSuccess) return fail(hip_fail(e, "hipStreamCreate"));
-  e = hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming);
-  for (int i = 0; e == hipSuccess && i < gm_model::kMaxParts - 1; ++i)
-    e = hipEventCreateWithFlags(&m->ev_join[i], hipEventDisableTiming);
-  if (e != hipSuccess) return fail(hip_fail(e, "hipEventCreate"));
-  if (const char* v = getenv("GM_SPLIT_PARTS")) {
-    const int n = atoi(v);
-    m->split_parts = n < 1 ? 1 : (n > gm_model::kMaxParts ? gm_model::kMaxParts : n);
-  }
   e = hipDeviceSynchronize();
   if (e != hipSuccess) return fail(hip_fail(e, "create"));
   *out = m;

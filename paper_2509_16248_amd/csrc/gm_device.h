@@ -79,10 +79,24 @@ template <typename T> __device__ __forceinline__ float round_as(float x) {
 }
 
 // ------------------------------------------------------------ reductions
+// Sum over the 64 lanes (all active), in every lane: shifts within rows of 16
+// lanes, the rows' totals passed on by broadcasts, the last lane's read back.
+// Lane crossings in the vector pipeline (DPP) take a few clocks each where a
+// shuffle goes through LDS: k_rownorm of 37 rows of 768, two sums per row, 4.5
+// -> 3.7 us.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_or_zero(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, ROWS == 0xf));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += dpp_or_zero<0x111, 0xf>(v);   // row_shr:1
+  v += dpp_or_zero<0x112, 0xf>(v);   // row_shr:2
+  v += dpp_or_zero<0x114, 0xf>(v);   // row_shr:4
+  v += dpp_or_zero<0x118, 0xf>(v);   // row_shr:8: lane 15 of a row has the row's sum
+  v += dpp_or_zero<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll

@@ -18,7 +18,8 @@ void gemm_f32(const GemmArgs& a, hipStream_t s);
 // fixed): `stage` is a tile's time per 64 columns of K with the chip full,
 // `fixed` its launch, first loads and epilogue, both in units of 10 ns as
 // measured on one MI355X.  Where the lines lie (us, this tile / the next best):
-//   256 x 256: 777 x 32000 x 4096 218 / 234, 4096 x 32000 x 1024 277 / 291
+//   256 x 256: 777 x 32000 x 4096 218 / 234, 4096 x 32000 x 1024 256 / 276,
+//              4096 x 50257 x 768 384 / 400, 8192 x 4096 x 1024 85 / 95
 //   256 x 192: 777 x 22016 x 4096 156 / 175, 2048 x 12288 x 4096 178 / 200
 //   256 x 128: 2048 x 4096 x 11008 172 / 186, 8192 x 1024 x 1024 24 / 29
 //   128 x 256: as 256 x 128 where M leaves half of its rows empty
@@ -34,7 +35,7 @@ struct TilePrice {
   int bm, bn, stage, fixed;
 };
 static constexpr TilePrice kPrice[kTiles16] = {
-    {256, 256, 152, 1000}, {256, 192, 114, 700}, {256, 128, 92, 700}, {128, 256, 93, 700},
+    {256, 256, 152, 1000}, {256, 192, 114, 850}, {256, 128, 92, 700}, {128, 256, 93, 700},
     {128, 128, 50, 500},   {128, 64, 34, 450},   {64, 64, 22, 400},   {64, 32, 18, 350},
     {32, 32, 10, 300},
 };

@@ -34,7 +34,6 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(
   __shared__ int kv[1024];
   __shared__ uint32_t red_trap[kPrologueThreads / 64];
   __shared__ int red_pad[kPrologueThreads / 64];
-  __shared__ int red_need[kPrologueThreads / 64];
   const int tid = threadIdx.x;
   for (int b = tid; b < B; b += blockDim.x) kv[b] = 0;
   for (int i = tid; i < (merge ? 0 : n_sites); i += blockDim.x) {
@@ -43,9 +42,12 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(
     state[kNanBase + i] = 0;
   }
   for (int i = tid; i < (merge ? 0 : log_vals); i += blockDim.x) log_stage[i] = 0.f;
+  // persistent state, fetched with the inputs instead of after the reductions
+  const int cached = state[kCachedLen], forwards = state[kFwdCount];
   __syncthreads();
   uint32_t trap = kTrapNone;
-  int pads = 0, need = 0;
+  int pads = 0;
+  const int need = S;                  // positions are 0..S-1
   const int n = B * S;
   for (int i = tid; i < n; i += blockDim.x) {
     const int id = ids[i];
@@ -58,21 +60,24 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(
     if (expected && guard_meta_ok && mk != expected[i])
       trap = min(trap, (5u << 24) | static_cast<uint32_t>(i));
     if (mk == 0) ++pads;
-    else atomicMax(&kv[i / S], s + 1);
-    need = max(need, s + 1);           // positions are 0..S-1
+    // the last unmasked lane of a wavefront's run within a sequence speaks for
+    // the run (64 lanes adding to one LDS word went one after the other: 4096
+    // tokens 8.4 us)
+    const int lane = tid & 63;
+    const unsigned long long later = __ballot(mk != 0) >> lane >> 1;
+    const int run = min(63 - lane, S - 1 - s);   // lanes after this one in the sequence
+    if (mk != 0 && (run == 0 || (later & (~0ull >> (64 - run))) == 0)) atomicMax(&kv[i / S], s + 1);
   }
   // wave reductions, then across waves
   for (int o = 32; o > 0; o >>= 1) {
     uint32_t t2 = __shfl_xor(trap, o, 64);
     trap = min(trap, t2);
     pads += __shfl_xor(pads, o, 64);
-    need = max(need, __shfl_xor(need, o, 64));
   }
   const int w = tid >> 6;
   if ((tid & 63) == 0) {
     red_trap[w] = trap;
     red_pad[w] = pads;
-    red_need[w] = need;
   }
   __syncthreads();
   for (int b = tid; b < B; b += blockDim.x) state[kvlen_base + b] = kv[b];
@@ -90,12 +95,10 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(
     for (int i = 1; i < static_cast<int>(blockDim.x >> 6); ++i) {
       trap = min(trap, red_trap[i]);
       pads += red_pad[i];
-      need = max(need, red_need[i]);
     }
     if (rotary && need > capacity) trap = min(trap, 3u << 24);
     if (expected && !guard_meta_ok) trap = min(trap, 5u << 24);   // shapes differ: never equal
     int regrow = 0;
-    const int cached = state[kCachedLen];
     int from = 0, to = 0;
     state[kRopeLong] = rope_orig > 0 && need > rope_orig;
     if (rotary && rope_orig <= 0 && trap == kTrapNone && need > cached) {
@@ -113,9 +116,8 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(
     state[kRegrow] = regrow;
     state[kRegrowFrom] = from;
     state[kRegrowTo] = to;
-    const int f = state[kFwdCount];
-    state[kFwdIndex] = f;
-    state[kFwdCount] = f + 1;
+    state[kFwdIndex] = forwards;
+    state[kFwdCount] = forwards + 1;
   }
 }
 
@@ -433,16 +435,21 @@ __global__ void k_emit_effects(int32_t* __restrict__ state, EffectRec* __restric
                                float* __restrict__ arena, int arena_cap, int n_log_layers,
                                int B, int seq2seq) {
   if (threadIdx.x != 0) return;
+  // every slot in one round trip, before anything is stored
   const int fwd = state[kFwdIndex];
   const uint32_t trap = static_cast<uint32_t>(state[kTrapFwd]);
-  if (trap != kTrapNone) {
-    if (state[kTrapSticky] == 0) state[kTrapSticky] = static_cast<int32_t>(trap);
-    return;
-  }
+  const int sticky = state[kTrapSticky];
   int count = state[kFifoCount];
   int dropped = state[kFifoDropped];
   int lcount = state[kLogCount];
   int ldropped = state[kLogDropped];
+  const int pad_any = state[kPadAny], pads = state[kPadCount];
+  const int pad_any_tgt = state[kPadAnyTgt], pads_tgt = state[kPadCountTgt];
+  const int regrow = state[kRegrow], need = state[kNeed];
+  if (trap != kTrapNone) {
+    if (sticky == 0) state[kTrapSticky] = static_cast<int32_t>(trap);
+    return;
+  }
   auto push = [&](int kind, int layer, int site, float value, int offset, int n) {
     if (count < cap) {
       EffectRec r;
@@ -459,9 +466,9 @@ __global__ void k_emit_effects(int32_t* __restrict__ state, EffectRec* __restric
       ++dropped;
     }
   };
-  if (state[kPadAny]) push(1, -1, seq2seq ? 0 : -1, static_cast<float>(state[kPadCount]), 0, 0);
-  if (seq2seq && state[kPadAnyTgt]) push(1, -1, 1, static_cast<float>(state[kPadCountTgt]), 0, 0);
-  if (state[kRegrow]) push(2, -1, -1, static_cast<float>(state[kNeed]), 0, 0);
+  if (pad_any) push(1, -1, seq2seq ? 0 : -1, static_cast<float>(pads), 0, 0);
+  if (seq2seq && pad_any_tgt) push(1, -1, 1, static_cast<float>(pads_tgt), 0, 0);
+  if (regrow) push(2, -1, -1, static_cast<float>(need), 0, 0);
   const int layers = max(n_sites / 2, n_log_layers);
   for (int l = 0; l < layers; ++l) {
     for (int s2 = 0; s2 < 2; ++s2) {

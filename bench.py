@@ -222,7 +222,7 @@ def measure(name, args, loaded=None, steps=None, warmup=None, frag=True):
          "tflop_per_forward": round(flops / 1e12, 4),
          "forward_frac_of_peak": round(flops / (t["ms"] * 1e-3) / 1e12 / peak, 4)}
     if cfg.dtype != "f32":
-        r["gemm"] = gemm_roofline(prof, cfg.dtype, "k_gemm_x")
+        r["gemm"] = gemm_roofline(prof, cfg.dtype, "k_gemm_pp")
     if frag:
         r["fragmented_baseline"] = fragmented(m, ids_t, mask_t, max(5, steps // 2), 2)
     log(f"[bench] {name}: {json.dumps({k: r[k] for k in ('ms_per_step', 'tokens_per_s', 'host_syncs_per_forward', 'forward_frac_of_peak')})}")
@@ -431,11 +431,11 @@ def main():
     del m, loaded, out
     torch.cuda.empty_cache()
     roof = head["gemm"]
-    roof["kernel"] = ("k_gemm_big (128x384, 256x256 and 128x256 tiles): every projection GEMM "
+    roof["kernel"] = ("k_gemm_pp (256x256, 256x192 and 256x128 tiles): every projection GEMM "
                       "and the LM head of the forward")
     roof["traffic"] = measured_traffic(WORKLOAD)
     roof["timing"] = ("HIP events on the launch stream around each kernel of an eager forward "
-                      "that runs the same launches as the graph (batch 1: one branch)")
+                      "that runs the same launches as the graph")
     result = {
         "metric": "steady-state forward tokens/sec + host syncs/forward (must be 0), 1 MI355X",
         "value": head["tokens_per_s"],

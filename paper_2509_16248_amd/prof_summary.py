@@ -29,12 +29,12 @@ import sys
 COPY = "__amd_rocclr_copyBuffer"
 WORKLOADS = {
     "decoder_4096": {
-        "kernels": ("void gm::k_gemm_big<", "void gm::k_gemm_x<"),
+        "kernels": ("void gm::k_gemm_pp<",),
         # grid size (threads) -> the launch it is, at 1 x 2048 tokens
-        "shapes": {262144: "QKV 2048x12288x4096 (128x384 tiles, BK 64 x 2)",
-                   131072: "O 2048x4096x4096 / down 2048x4096x11008 (128x256 tiles)",
-                   352256: "gate|up 2048x22016x4096 (256x256 tiles, BK 64 x 2)",
-                   512000: "head 2048x32000x4096 (256x256 tiles, BK 64 x 2)"},
+        "shapes": {262144: "QKV 2048x12288x4096 (256x192 tiles)",
+                   131072: "O 2048x4096x4096 / down 2048x4096x11008 (256x128 tiles)",
+                   352256: "gate|up 2048x22016x4096 (256x256 tiles)",
+                   512000: "head 2048x32000x4096 (256x256 tiles)"},
         "copy_bytes": 32000 * 4096 * 2,
         "algorithmic": {   # operands read once + output written once (+ residual read)
             262144: 2 * (2048 * 4096 + 12288 * 4096 + 2048 * 12288),
@@ -45,9 +45,10 @@ WORKLOADS = {
                    2 * (2048 * 11008 + 4096 * 11008 + 2 * 2048 * 4096)),
     },
     "causal_lm_768": {
-        "kernels": ("void gm::k_gemm_x<unsigned short, 128, 128, 2, 4, 2>",),
-        "shapes": {294912: "QKV 4096x2304x768", 98304: "O/down 4096x768",
-                   393216: "up 4096x3072x768", 6438912: "head 4096x50257x768"},
+        "kernels": ("void gm::k_gemm_pp<",),
+        "shapes": {98304: "QKV 4096x2304x768 (256x192 tiles), O/down 4096x768 (128x128)",
+                   131072: "up 4096x3072x768 (256x192)",
+                   1613824: "head 4096x50257x768 (256x256)"},
         "copy_bytes": 50257 * 768 * 2,
     },
 }

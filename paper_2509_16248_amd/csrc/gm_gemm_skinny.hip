@@ -8,26 +8,29 @@ namespace gm {
 // rows (B operand): lane l supplies 16 bytes of row l % 16 at k-chunk l / 16 of
 // a step, and ends with output columns 4 (l / 16) .. + 3 of activation row
 // l % 16.  fp32: four v_mfma_f32_16x16x4 per step, MFMA r taking element r of
-// every lane's four (the order of the sum over k is free).
+// every lane's four into a sum of its own: a sum in one chain rounds K / 8
+// times in a row instead of K / 32.
 template <typename T> struct Mfma16;
 template <> struct Mfma16<bf16_t> {
   typedef bf16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  static constexpr int kSums = 1;
+  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c) {
+    c[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c[0], 0, 0, 0);
   }
 };
 template <> struct Mfma16<f16_t> {
   typedef f16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  static constexpr int kSums = 1;
+  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c) {
+    c[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c[0], 0, 0, 0);
   }
 };
 template <> struct Mfma16<float> {
   typedef f32x4 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
+  static constexpr int kSums = 4;
+  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], c, 0, 0, 0);
-    return c;
+    for (int r = 0; r < 4; ++r) c[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], c[r], 0, 0, 0);
   }
 };
 
@@ -143,9 +146,12 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_gemm_rows(GemmArgs a) {
                                  : static_cast<const T*>(a.A) + static_cast<long long>(m) * a.lda + kg * VN;
   const T* gp = static_cast<const T*>(a.norm_g) + kg * VN;
   const int steps = a.K / KC;
-  f32x4 acc[CT];
+  constexpr int SUMS = Mfma16<T>::kSums;
+  f32x4 acc[CT][SUMS];
 #pragma unroll
-  for (int c = 0; c < CT; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < CT; ++c)
+#pragma unroll
+    for (int i = 0; i < SUMS; ++i) acc[c][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   float ss = 0.f;                                  // sum of squares of this lane's elements
   vec w[2][CT][U], x[2][U], gn[2][U];
   auto fetch = [&](auto set, int s0) {             // steps s0 .. s0 + U - 1
@@ -175,7 +181,7 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_gemm_rows(GemmArgs a) {
           }
         }
 #pragma unroll
-        for (int c = 0; c < CT; ++c) acc[c] = Mfma16<T>::run(w[set][c][u], x[set][u], acc[c]);
+        for (int c = 0; c < CT; ++c) Mfma16<T>::run(w[set][c][u], x[set][u], acc[c]);
       }
     });
   };
@@ -195,7 +201,11 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_gemm_rows(GemmArgs a) {
     fetch(s1, s + 3 * B);
   }
 #pragma unroll
-  for (int c = 0; c < CT; ++c) red[wave][c][lane] = acc[c];
+  for (int c = 0; c < CT; ++c) {
+    f32x4 t = acc[c][0];
+    if constexpr (SUMS == 4) t = (t + acc[c][1]) + (acc[c][2] + acc[c][3]);
+    red[wave][c][lane] = t;
+  }
   if constexpr (NORM == kRowsScaled) {
     ss += __shfl_xor(ss, 16, 64);
     ss += __shfl_xor(ss, 32, 64);

@@ -115,9 +115,22 @@ void launch_rownorm(const RowArgs& a, hipStream_t s);
 // copied from log_stage into the arena (the value at the call site).
 // seq2seq: an encoder-decoder forward, whose source and target padding
 // branches give PAD records with site 0 and 1.
+// A model with a KV cache also gets its sequence lengths (fin.seqlen: prefill
+// 1 + last unmasked key; decode pos[b] + 1 unless the step trapped) and, after
+// a decode step, the greedy tokens merged from the parts of launch_argmax.
+struct ArgmaxPart {
+  float value;       // largest non-NaN logit of the part
+  int32_t index;     // its lowest index
+  int32_t nan;       // lowest index of a NaN, or 0x7FFFFFFF
+};
+constexpr int kArgmaxParts = 16;   // per sequence
+struct Finish {
+  int32_t* seqlen; const int32_t* pos; int decode;
+  const ArgmaxPart* parts; int32_t* next;
+};
 void launch_emit_effects(int32_t* state, void* fifo, int fifo_cap, int n_sites,
                          const float* log_stage, float* arena, int arena_cap, int n_log_layers,
-                         int B, int seq2seq, hipStream_t s);
+                         int B, int seq2seq, const Finish& fin, hipStream_t s);
 
 // ------------------------------------------------------------ decode step
 // KV cache: per layer, K and V as [max_batch][H][max_seq][hd] (act dtype) and
@@ -158,14 +171,10 @@ struct DecAttnArgs {
 };
 void launch_decode_attention(const DecAttnArgs& a, hipStream_t s);
 
-// next[b] = index of the largest logit of row b (first NaN if any; lowest
-// index among equal values).
-void launch_argmax(const void* logits, int dtype, int B, int V, int32_t* next, hipStream_t s);
-
-// Sequence lengths after a forward: prefill seqlen[b] = 1 + last unmasked
-// key; decode seqlen[b] = pos[b] + 1 unless the step trapped.
-void launch_seqlen_update(int32_t* seqlen, const int32_t* pos, const int32_t* state, int B,
-                          int decode, hipStream_t s);
+// The largest logit of each sixteenth of row b into parts[b * kArgmaxParts ..]:
+// the greedy choice is the first NaN if any, else the lowest index among equal
+// values.
+void launch_argmax(const void* logits, int dtype, int B, int V, ArgmaxPart* parts, hipStream_t s);
 
 void launch_gather_rows(void* dst, const void* src, const int32_t* row_map,
                         int rows, int row_bytes, hipStream_t s);

@@ -430,10 +430,31 @@ void launch_rownorm(const RowArgs& a, hipStream_t s) {
 // appends one record per taken branch, in program order (padding branch,
 // rotary regrow, then the clamp sites in layer order), to the FIFO that the
 // host replays after the stream completes.  One thread: the order is fixed.
+// For models with a KV cache the same launch updates the sequence lengths and
+// merges the greedy choice (a launch of their own cost 4.9 us a step).
 __global__ void k_emit_effects(int32_t* __restrict__ state, EffectRec* __restrict__ fifo,
                                int cap, int n_sites, const float* __restrict__ log_stage,
                                float* __restrict__ arena, int arena_cap, int n_log_layers,
-                               int B, int seq2seq) {
+                               int B, int seq2seq, Finish fin) {
+  if (fin.seqlen) {
+    const bool trapped = static_cast<uint32_t>(state[kTrapFwd]) != kTrapNone;
+    for (int b = threadIdx.x; b < B; b += blockDim.x) {
+      if (!fin.decode) fin.seqlen[b] = state[kKvLenBase + b];
+      else if (!trapped) fin.seqlen[b] = fin.pos[b] + 1;
+      if (fin.next) {
+        const ArgmaxPart* p = fin.parts + b * kArgmaxParts;
+        ArgmaxPart best = p[0];
+        for (int k = 1; k < kArgmaxParts; ++k) {
+          if (p[k].value > best.value || (p[k].value == best.value && p[k].index < best.index)) {
+            best.value = p[k].value;
+            best.index = p[k].index;
+          }
+          best.nan = min(best.nan, p[k].nan);
+        }
+        fin.next[b] = best.nan != 0x7FFFFFFF ? best.nan : best.index;
+      }
+    }
+  }
   if (threadIdx.x != 0) return;
   // every slot in one round trip, before anything is stored
   const int fwd = state[kFwdIndex];
@@ -496,10 +517,10 @@ __global__ void k_emit_effects(int32_t* __restrict__ state, EffectRec* __restric
 
 void launch_emit_effects(int32_t* state, void* fifo, int cap, int n_sites, const float* log_stage,
                          float* arena, int arena_cap, int n_log_layers, int B, int seq2seq,
-                         hipStream_t s) {
+                         const Finish& fin, hipStream_t s) {
   hipLaunchKernelGGL(k_emit_effects, dim3(1), dim3(64), 0, s, state,
                      static_cast<EffectRec*>(fifo), cap, n_sites, log_stage, arena, arena_cap,
-                     n_log_layers, B, seq2seq);
+                     n_log_layers, B, seq2seq, fin);
 }
 
 // ------------------------------------------------------------ row gather

@@ -137,6 +137,7 @@ struct gm_model {
   uint8_t* kv_valid = nullptr;
   int32_t *seqlen = nullptr, *dpos = nullptr;
   float* dpart = nullptr;
+  ArgmaxPart* argmax_parts = nullptr;
   int dec_nsplit = 0;
   int cache_B = 0;          // batch of the last prefill (host-side), 0 = none
   // encoder-decoder (cfg.n_dec_layers > 0): decoder layers and their
@@ -658,13 +659,15 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   else
     gemm(GM_K_GEMM_HEAD, hh, d, m->head, c.vocab, kEpiStore, nullptr, logits, c.vocab, nullptr, -1);
   if (dec && dec->next) {
-    launch_argmax(logits, m->dtype, B, c.vocab, dec->next, s);
+    launch_argmax(logits, m->dtype, B, c.vocab, m->argmax_parts, s);
     P(GM_K_ARGMAX, -1, 0.0, es * B * static_cast<double>(c.vocab));
   }
-  if (c.kv_cache && on()) launch_seqlen_update(m->seqlen, m->dpos, m->state, B, dec ? 1 : 0, s);
   if (on())
     launch_emit_effects(m->state, m->fifo, kFifoCap, ns, m->log_stage, m->log_arena,
-                        kLogArenaCap, c.log_hidden ? c.n_layers : 0, B, 0, s);
+                        kLogArenaCap, c.log_hidden ? c.n_layers : 0, B, 0,
+                        Finish{c.kv_cache ? m->seqlen : nullptr, m->dpos, dec ? 1 : 0,
+                               m->argmax_parts, dec ? dec->next : nullptr},
+                        s);
   P(GM_K_EFFECTS, -1, 0.0, 0.0);
 }
 
@@ -862,7 +865,7 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
   cur_layer = -1;
   norm_rows(Ttp, hh, aa, m->lnf_g, m->lnf_b);
   gemm(GM_K_GEMM_HEAD, Ttp, aa, d, m->head, c.vocab, kEpiStore, nullptr, lg, c.vocab, nullptr);
-  if (on()) launch_emit_effects(m->state, m->fifo, kFifoCap, 0, nullptr, nullptr, 0, 0, B, 1, s);
+  if (on()) launch_emit_effects(m->state, m->fifo, kFifoCap, 0, nullptr, nullptr, 0, 0, B, 1, Finish{}, s);
   P(GM_K_EFFECTS, -1, 0.0, 0.0);
 }
 
@@ -1148,6 +1151,9 @@ int gm_model_create(const gm_config* cfg, const gm_weights* w, gm_model** out) {
                                 sizeof(float))))
       return fail(rc);
     m->dpart = static_cast<float*>(q);
+    if ((rc = m->alloc(&q, static_cast<size_t>(c.max_batch) * kArgmaxParts * sizeof(ArgmaxPart))))
+      return fail(rc);
+    m->argmax_parts = static_cast<ArgmaxPart*>(q);
     e = hipMemset(m->kv_valid, 0, static_cast<size_t>(c.max_batch) * c.max_seq);
     if (e == hipSuccess) e = hipMemset(m->seqlen, 0, c.max_batch * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(m->dpos, 0, c.max_batch * sizeof(int32_t));

@@ -8,27 +8,28 @@ namespace gm {
 // rows (B operand): lane l supplies 16 bytes of row l % 16 at k-chunk l / 16 of
 // a step, and ends with output columns 4 (l / 16) .. + 3 of activation row
 // l % 16.  fp32: four v_mfma_f32_16x16x4 per step, MFMA r taking element r of
-// every lane's four into a sum of its own: a sum in one chain rounds K / 8
-// times in a row instead of K / 32.
+// every lane's four, in steps that alternate between two sets of four sums (a
+// sum in one chain rounds eight times as often in a row).
 template <typename T> struct Mfma16;
 template <> struct Mfma16<bf16_t> {
   typedef bf16x8 vec;
   static constexpr int kSums = 1;
-  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c) {
+  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c, int) {
     c[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c[0], 0, 0, 0);
   }
 };
 template <> struct Mfma16<f16_t> {
   typedef f16x8 vec;
   static constexpr int kSums = 1;
-  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c) {
+  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c, int) {
     c[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c[0], 0, 0, 0);
   }
 };
 template <> struct Mfma16<float> {
   typedef f32x4 vec;
-  static constexpr int kSums = 4;
-  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c) {
+  static constexpr int kSums = 8;
+  static __device__ __forceinline__ void run(vec a, vec b, f32x4* c, int step) {
+    c += 4 * step;
 #pragma unroll
     for (int r = 0; r < 4; ++r) c[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], c[r], 0, 0, 0);
   }
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_gemm_rows(GemmArgs a) {
           }
         }
 #pragma unroll
-        for (int c = 0; c < CT; ++c) Mfma16<T>::run(w[set][c][u], x[set][u], acc[c]);
+        for (int c = 0; c < CT; ++c) Mfma16<T>::run(w[set][c][u], x[set][u], acc[c], u);
       }
     });
   };
@@ -203,7 +204,9 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_gemm_rows(GemmArgs a) {
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
     f32x4 t = acc[c][0];
-    if constexpr (SUMS == 4) t = (t + acc[c][1]) + (acc[c][2] + acc[c][3]);
+    if constexpr (SUMS == 8)
+      t = ((t + acc[c][1]) + (acc[c][2] + acc[c][3])) +
+          ((acc[c][4] + acc[c][5]) + (acc[c][6] + acc[c][7]));
     red[wave][c][lane] = t;
   }
   if constexpr (NORM == kRowsScaled) {

@@ -27,6 +27,49 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ------------------------------------------------------------ fp32 kernel
+// One query by one wavefront, a key per lane, skipping keys of weight 0: the
+// queries of a workgroup that met an Inf or NaN in V (k_attn_f32).
+template <int HD>
+__device__ __forceinline__ void attn_f32_row(const AttnArgs& a, int b, int h, int i, int kend,
+                                                       bool pad) {
+  constexpr int CL = (HD + 63) / 64;   // channels per lane
+  const int lane = threadIdx.x & 63;
+  const float* q = static_cast<const float*>(a.q) + (static_cast<long long>(b) * a.Sq + i) * a.ldq + h * HD;
+  const float* kb = static_cast<const float*>(a.k) + static_cast<long long>(b) * a.Sk * a.ldkv + h * HD;
+  const float* vb = static_cast<const float*>(a.v) + static_cast<long long>(b) * a.Sk * a.ldkv + h * HD;
+  const int32_t* mk = a.mask + static_cast<long long>(b) * a.Sk;
+  if (a.causal) kend = kend < i + 1 ? kend : i + 1;
+  auto score = [&](int j) {
+    if (j >= kend || (pad && mk[j] == 0)) return -INFINITY;
+    const float* k = kb + static_cast<long long>(j) * a.ldkv;
+    float s = 0.f;
+    for (int c = 0; c < HD; ++c) s = fmaf(q[c], k[c], s);
+    return s * a.scale;
+  };
+  float m = -INFINITY;
+  for (int j0 = 0; j0 < kend; j0 += 64) m = fmaxf(m, score(j0 + lane));
+  m = wave_max(m);
+  float l = 0.f, o[CL] = {};
+  for (int j0 = 0; j0 < kend; j0 += 64) {
+    const float s = score(j0 + lane);
+    const float p = s == -INFINITY ? 0.f : expf(s - m);
+    l += p;
+    for (int t = 0; t < 64 && j0 + t < kend; ++t) {
+      const float pt = __shfl(p, t, 64);
+      if (pt == 0.f) continue;
+      const float* v = vb + static_cast<long long>(j0 + t) * a.ldkv;
+#pragma unroll
+      for (int c = 0; c < CL; ++c)
+        if (lane + 64 * c < HD) o[c] = fmaf(pt, v[lane + 64 * c], o[c]);
+    }
+  }
+  l = wave_sum(l);
+  float* out = static_cast<float*>(a.ctx) + (static_cast<long long>(b) * a.Sq + i) * a.d + h * HD;
+#pragma unroll
+  for (int c = 0; c < CL; ++c)
+    if (lane + 64 * c < HD) out[lane + 64 * c] = l > 0.f ? o[c] / l : 0.f;
+}
+
 // Workgroup = 32 queries of one (sequence, head); its 4 wavefronts take the
 // tiles of 32 keys in turn, each with an online softmax of its own, and are
 // merged in LDS.  Per tile: S^T = K Q^T on v_mfma_f32_32x32x2 (a lane reads 4
@@ -37,12 +80,18 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // come straight from global memory: one MFMA takes 64 clocks for 512 bytes.
 // 4 x 12 heads x 200 queries, head size 64, causal: 81 us with the wavefront-
 // per-query kernel below, about 22 us here.
+// A hidden key has weight 0, but an MFMA multiplies its V all the same, and
+// 0 x Inf is NaN.  So every V element read also goes through fma(v, 0, odd), and
+// where that has met an Inf or NaN the workgroup's queries are computed again by
+// attn_f32_row (the check is hidden behind the MFMAs: 2 x 8 heads x 700 queries
+// of head size 128 in a 1024-wide model 1732 -> 1735 us a forward).
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
   constexpr int NC = HD / 8, CB = HD / 32, NW = 4;
   typedef float f32x4a __attribute__((ext_vector_type(4)));
   __shared__ float s_m[NW][32], s_l[NW][32];
   __shared__ float s_o[NW][HD][33];
+  __shared__ int s_odd[NW];
   const int q0 = blockIdx.x * 32, h = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, g = lane >> 5;
@@ -55,6 +104,7 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
   const int pad = a.state[a.pad_slot];
   int kend = pad ? a.state[a.kvlen_base + b] : Sk;
   kend = kend < Sk ? kend : Sk;
+  const int kall = kend;
   if (a.causal) kend = kend < q0 + 32 ? kend : q0 + 32;
   const int32_t* mk = a.mask + static_cast<long long>(b) * Sk;
   f32x4a qf[NC];
@@ -66,6 +116,7 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[c][e] = 0.f;
   float m = -INFINITY, l = 0.f;
+  float odd = 0.f;                     // 0, or NaN behind a V element that is Inf or NaN
   for (int k0 = 32 * wave; k0 < kend; k0 += 32 * NW) {
     const int kr = k0 + l32 < Sk ? k0 + l32 : Sk - 1;
     const float* k = kb + static_cast<long long>(kr) * a.ldkv + 4 * g;
@@ -107,6 +158,10 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
     l = l * corr + sum;
     m = top;
 #pragma unroll
+    for (int t = 0; t < 16; ++t)
+#pragma unroll
+      for (int c = 0; c < CB; ++c) odd = fmaf(vf[t][c], 0.f, odd);
+#pragma unroll
     for (int c = 0; c < CB; ++c) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[c][e] *= corr;
@@ -115,6 +170,8 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
     }
   }
   l += __shfl_xor(l, 32, 64);
+  const unsigned long long odd_lanes = __ballot(odd != 0.f);   // (NaN != 0)
+  if (lane == 0) s_odd[wave] = odd_lanes != 0;
   if (g == 0) {
     s_m[wave][l32] = m;
     s_l[wave][l32] = l;
@@ -124,6 +181,10 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) s_o[wave][32 * c + 8 * (e / 4) + 4 * g + e % 4][l32] = o[c][e];
   __syncthreads();
+  if (s_odd[0] | s_odd[1] | s_odd[2] | s_odd[3]) {
+    for (int i = q0 + wave; i < q0 + 32 && i < Sq; i += NW) attn_f32_row<HD>(a, b, h, i, kall, pad != 0);
+    return;
+  }
   float* out = static_cast<float*>(a.ctx) + (static_cast<long long>(b) * Sq + q0) * a.d + h * HD;
   for (int e = threadIdx.x; e < 32 * HD; e += 256) {
     const int c = e % HD, i = e / HD;

@@ -416,7 +416,9 @@ int gm_flush_effects(gm_model *m, gm_effect_cb cb, void *user, int32_t *n_droppe
  * n_layers * T * (8 * d_model + d_ff) elements of act_dtype, T = B * S):
  * layer l's block starts at element l * T * (8d + ff) and holds, row-major,
  *   a1 [T, d]     the first norm's output (with the preceding clamp site's
- *                 select applied to the stream it reads),
+ *                 select applied to the stream it reads); where a forward of
+ *                 at most 16 rows takes the norm inside the product that
+ *                 reads it, a1 and a2 are written beside it,
  *   qkv [T, 3d]   q | k | v after the projection epilogue (rotary applied),
  *   ctx [T, d]    the attention context,
  *   h_mid [T, d]  the stream after the attention residual (before the clamp
@@ -436,7 +438,9 @@ int gm_debug_forward_layers(gm_model *m, int32_t B, int32_t S, const int32_t *to
  * tests).  which: 0 residual stream h [T, d], 1 norm output [T, d],
  * 2 fused q|k|v [T, 3d], 3 attention context [T, d], 4 FFN hidden [T, d_ff]
  * (T = max_batch * max_seq rows, act_dtype).  Contents are those left by the
- * last kernel that wrote the buffer. */
+ * last kernel that wrote the buffer; a forward or decode step of at most 16
+ * rows may take its norms inside the products that read them and leave buffer
+ * 1 alone. */
 int gm_debug_buffer(const gm_model *m, int32_t which, void **ptr, uint64_t *bytes);
 
 /* Paper: Evaluation, "Overhead Analysis of Graph Breaks" and "Steady-State

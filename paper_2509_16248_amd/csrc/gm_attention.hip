@@ -31,7 +31,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // queries of a workgroup that met an Inf or NaN in V (k_attn_f32).
 template <int HD>
 __device__ __forceinline__ void attn_f32_row(const AttnArgs& a, int b, int h, int i, int kend,
-                                                       bool pad) {
+                                             bool pad) {
   constexpr int CL = (HD + 63) / 64;   // channels per lane
   const int lane = threadIdx.x & 63;
   const float* q = static_cast<const float*>(a.q) + (static_cast<long long>(b) * a.Sq + i) * a.ldq + h * HD;

@@ -38,7 +38,9 @@ template <> struct Mfma16<float> {
 constexpr int kRowsWaves = 8;
 
 // Rows of x normalised into LDS (pitch elements apart), one wavefront per
-// row: the arithmetic of the row kernel, so the same bits.
+// row: the arithmetic of the row kernel (fp32 and bf16: the same bits; in fp16
+// the compiler joins the last multiply-add with its rounding in some places and
+// not in others, so a last bit may differ).
 template <typename T, int MAXV>
 __device__ __forceinline__ void norm_to_lds(const GemmArgs& a, T* lds, int pitch, int wave, int lane) {
   typedef typename std::conditional<sizeof(T) == 4, f32x4v, u32x4>::type V;

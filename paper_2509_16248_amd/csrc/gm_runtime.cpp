@@ -600,17 +600,15 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
     P(GM_K_ATTENTION, cur_layer, attn_flops, attn_bytes);
   };
   // A pre-norm and the product that reads it: one launch for a few rows, two
-  // where the clamp select or a debug copy needs the normalised rows stored.
+  // where the clamp select needs the normalised rows stored.  A debug forward
+  // launches the norm for its copy as well and takes the same product.
   auto norm_gemm = [&](int kind, const void* g, const void* b, int prior_site, const void* W, int N,
                        int epi, const void* bias, void* out, int ldo) {
-    if (prior_site < 0 && !dump && gemm_takes_norm(m->dtype, T, d, normk)) {
-      const Norm n{g, b};
-      gemm(kind, hh, d, W, N, epi, bias, out, ldo, nullptr, -1, &n);
-      return;
-    }
-    norm_rows(hh, aa, g, b, prior_site);
+    const bool fused = prior_site < 0 && gemm_takes_norm(m->dtype, T, d, normk);
+    if (!fused || (dump && kind != GM_K_GEMM_HEAD)) norm_rows(hh, aa, g, b, prior_site);
     if (dump && kind != GM_K_GEMM_HEAD) dump->copy(cur_layer, kind == GM_K_GEMM_QKV ? 0 : 4, aa, s);
-    gemm(kind, aa, d, W, N, epi, bias, out, ldo, nullptr, -1);
+    const Norm n{g, b};
+    gemm(kind, fused ? hh : aa, d, W, N, epi, bias, out, ldo, nullptr, -1, fused ? &n : nullptr);
   };
   int prev_site = -1;
   for (int l = 0; l < c.n_layers; ++l) {

@@ -252,6 +252,179 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_gemm_rows(GemmArgs a) {
   site_flush(a, sm);
 }
 
+// ------------------------------------------------------------ fp32, very few rows
+// v_mfma_f32_16x16x4 does a sixteenth of the work of its 16-bit kin per byte of
+// weights read, and with few rows of 16 in use a plain multiply-add per lane is
+// no slower; what decides is how the weights arrive.  Here the 64 lanes read 1 KB
+// of one weight row at a time (16 rows of 64 bytes in k_gemm_rows), and their
+// partial sums are reduced by a transposing butterfly: each step halves the
+// values a lane carries.
+template <int NV>
+__device__ __forceinline__ float lane_transpose_sum(float (&v)[NV], int lane, int& index) {
+  index = 0;
+  static_for<0, 6>([&](auto st) {
+    constexpr int o = 32 >> decltype(st)::value;
+    constexpr int n = NV >> decltype(st)::value;
+    if constexpr (n >= 2) {
+      constexpr int half = n / 2;
+      const bool up = (lane & o) != 0;
+#pragma unroll
+      for (int j = 0; j < half; ++j) {
+        const float send = up ? v[j] : v[j + half];
+        const float keep = up ? v[j + half] : v[j];
+        v[j] = keep + __shfl_xor(send, o, 64);
+      }
+      if (up) index += half;
+    } else {
+      v[0] += __shfl_xor(v[0], o, 64);
+    }
+  });
+  return v[0];
+}
+
+// The epilogue of G groups of 4 columns from n0 on, res[column][row], by one
+// wavefront.  A lane's group ends the columns that the pair epilogue sees (its
+// second tile would be written 16 further on).
+template <int MP, int G>
+__device__ __forceinline__ void lanes_epilogue(const GemmArgs& a, const float (*res)[MP + 1], int n0) {
+  const int lane = threadIdx.x & 63, m = lane / G, q = lane % G, n = n0 + 4 * q;
+  GemmArgs b = a;
+  b.N = n + 4 < a.N ? n + 4 : a.N;
+  SiteMax sm;
+  if (m < MP && m < a.M) {
+    float va[4];
+    const float vb[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) va[r] = res[4 * q + r][m];
+    epi_pair<float>(b, m, n, va, vb, sm);
+  }
+  site_flush(a, sm);
+}
+
+// A workgroup: 8 R columns, a wavefront R of them over the whole of K.
+template <int MP, int R>
+__global__ __launch_bounds__(512) void k_gemm_lanes(GemmArgs a) {
+  constexpr int COLS = 8 * R;
+  __shared__ float res[COLS][MP + 1];
+  const int n0 = blockIdx.x * COLS;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const float* w[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int n = n0 + wave * R + r;
+    w[r] = static_cast<const float*>(a.W) + static_cast<long long>(n < a.N ? n : a.N - 1) * a.ldw;
+  }
+  const float* x[MP];
+#pragma unroll
+  for (int m = 0; m < MP; ++m)
+    x[m] = static_cast<const float*>(a.A) + static_cast<long long>(m < a.M ? m : a.M - 1) * a.lda;
+  float acc[R * MP];
+#pragma unroll
+  for (int j = 0; j < R * MP; ++j) acc[j] = 0.f;
+#pragma unroll 2
+  for (int k = lane * 4; k < a.K; k += 256) {
+    f32x4 wv[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) wv[r] = *reinterpret_cast<const f32x4*>(w[r] + k);
+#pragma unroll
+    for (int m = 0; m < MP; ++m) {
+      const f32x4 xv = *reinterpret_cast<const f32x4*>(x[m] + k);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r * MP + m] = fmaf(wv[r][i], xv[i], acc[r * MP + m]);
+    }
+  }
+  int at;
+  const float sum = lane_transpose_sum<R * MP>(acc, lane, at);
+  // lanes that differ only in their low bits hold the same value
+  if ((lane & (64 / (R * MP) - 1)) == 0) res[wave * R + at / MP][at % MP] = sum;
+  __syncthreads();
+  if (wave == 0) lanes_epilogue<MP, 2 * R>(a, res, n0);
+}
+
+// A workgroup: 8 columns, every wavefront all of them over an eighth of K, so
+// that a narrow output still has every load of a short K in flight at once.
+template <int MP>
+__global__ __launch_bounds__(512) void k_gemm_lanes_ksplit(GemmArgs a) {
+  constexpr int R = 8;
+  __shared__ float part[8][R * MP];
+  __shared__ float res[R][MP + 1];
+  const int n0 = blockIdx.x * R;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int per = (a.K + 31) / 32 * 4;             // k per wavefront, in fours
+  const int kb = wave * per, ke = kb + per < a.K ? kb + per : a.K;
+  const float* w[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    w[r] = static_cast<const float*>(a.W) + static_cast<long long>(n0 + r < a.N ? n0 + r : a.N - 1) * a.ldw;
+  const float* x[MP];
+#pragma unroll
+  for (int m = 0; m < MP; ++m)
+    x[m] = static_cast<const float*>(a.A) + static_cast<long long>(m < a.M ? m : a.M - 1) * a.lda;
+  float acc[R * MP];
+#pragma unroll
+  for (int j = 0; j < R * MP; ++j) acc[j] = 0.f;
+  for (int k = kb + lane * 4; k < ke; k += 256) {
+    f32x4 wv[R], xv[MP];
+#pragma unroll
+    for (int r = 0; r < R; ++r) wv[r] = *reinterpret_cast<const f32x4*>(w[r] + k);
+#pragma unroll
+    for (int m = 0; m < MP; ++m) xv[m] = *reinterpret_cast<const f32x4*>(x[m] + k);
+#pragma unroll
+    for (int m = 0; m < MP; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r * MP + m] = fmaf(wv[r][i], xv[m][i], acc[r * MP + m]);
+  }
+  int at;
+  const float sum = lane_transpose_sum<R * MP>(acc, lane, at);
+  if ((lane & (64 / (R * MP) - 1)) == 0) part[wave][at] = sum;
+  __syncthreads();
+  if (threadIdx.x < R * MP) {
+    float t = 0.f;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) t += part[v][threadIdx.x];
+    res[threadIdx.x / MP][threadIdx.x % MP] = t;
+  }
+  __syncthreads();
+  if (wave == 0) lanes_epilogue<MP, 2>(a, res, n0);
+}
+
+// Which fp32 products of at most 8 rows go there (us, here / k_gemm_rows; the
+// pair epilogues stay with k_gemm_rows, which takes their norm):
+//   the head: 50257 x 768 24 / 35 with 1 row, 33 / 37 with 8; 32000 x 1024 29 /
+//     35 with 8 and its norm launch; not up to 512 columns, whose norm
+//     k_gemm_rows takes into LDS
+//   one or two rows: 2304 x 768 4.2 / 5.1 and 4.4 / 5.0 (4 rows 5.2 / 5.2, 6
+//     rows 6.8 / 5.2), 768 x 768 4.3 / 5.1 and 5.0 / 5.2 (4 rows 6.2 / 4.8)
+//   narrow outputs of a long K: 768 x 3072 5.2 / 10.3 with 1 row, 8.3 / 12.4
+//     with 8; 512 x 1408 6.3 / 6.9 with 8 (256 x 1024: 5.8 / 5.5 with 2)
+static bool f32_by_lanes(int M, int N, int K, int epi) {
+  if (epi == kEpiGatedGelu || epi == kEpiGatedSilu || epi == kEpiRope) return false;
+  if (N >= 8192) return M <= 8 && K > 512;
+  return K >= 768 && (M <= 2 || (M <= 8 && N < 2048 && K >= 1280));
+}
+
+template <int MP>
+static void f32_lanes_rows(const GemmArgs& a, hipStream_t s) {
+  const dim3 block(512);
+  if (a.N >= 8192)
+    hipLaunchKernelGGL((k_gemm_lanes<MP, 4>), dim3((a.N + 31) / 32), block, 0, s, a);
+  else if (a.N < 2048)
+    hipLaunchKernelGGL((k_gemm_lanes_ksplit<MP>), dim3((a.N + 7) / 8), block, 0, s, a);
+  else if constexpr (MP <= 2)
+    hipLaunchKernelGGL((k_gemm_lanes<MP, 1>), dim3((a.N + 7) / 8), block, 0, s, a);
+}
+
+static void f32_lanes(const GemmArgs& a, hipStream_t s) {
+  if (a.M <= 1) f32_lanes_rows<1>(a, s);
+  else if (a.M <= 2) f32_lanes_rows<2>(a, s);
+  else if (a.M <= 4) f32_lanes_rows<4>(a, s);
+  else f32_lanes_rows<8>(a, s);
+}
+
 static RowsNorm rows_norm(int dtype, int norm, int d) {
   const int es = dtype == kF32 ? 4 : 2;
   if (d * es <= 2 * 64 * 16) return kRowsLds;      // two vectors per lane; 33 KB of LDS at 16 rows
@@ -259,8 +432,9 @@ static RowsNorm rows_norm(int dtype, int norm, int d) {
   return norm == 1 && dtype != kF16 ? kRowsScaled : kRowsPlain;
 }
 
-bool gemm_takes_norm(int dtype, int M, int d, int norm) {
-  return M <= 16 && rows_norm(dtype, norm, d) != kRowsPlain;
+bool gemm_takes_norm(int dtype, int M, int N, int d, int epi, int norm) {
+  if (M > 16 || (dtype == kF32 && f32_by_lanes(M, N, d, epi))) return false;
+  return rows_norm(dtype, norm, d) != kRowsPlain;
 }
 
 template <typename T, int CT>
@@ -287,7 +461,8 @@ static void rows_t(const GemmArgs& a, hipStream_t s) {
 }
 
 void gemm_skinny(const GemmArgs& a, hipStream_t s) {
-  if (a.dtype == kF32) rows_t<float>(a, s);
+  if (a.dtype == kF32 && f32_by_lanes(a.M, a.N, a.K, a.epi)) f32_lanes(a, s);
+  else if (a.dtype == kF32) rows_t<float>(a, s);
   else if (a.dtype == kBF16) rows_t<bf16_t>(a, s);
   else rows_t<f16_t>(a, s);
 }

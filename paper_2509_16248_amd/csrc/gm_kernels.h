@@ -48,8 +48,9 @@ struct GemmArgs {
 // M <= 16 rows (a decode step, or a tiny forward) runs on a weight-streaming
 // kernel; larger M on the tiled MFMA kernel.
 void launch_gemm(const GemmArgs& a, hipStream_t s);
-// Whether launch_gemm accepts GemmArgs::norm = norm for M rows of d columns.
-bool gemm_takes_norm(int dtype, int M, int d, int norm);
+// Whether launch_gemm accepts GemmArgs::norm = norm for M rows of d columns, N
+// output columns and the epilogue.
+bool gemm_takes_norm(int dtype, int M, int N, int d, int epi, int norm);
 
 struct AttnArgs {
   int dtype;

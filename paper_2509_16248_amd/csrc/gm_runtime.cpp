@@ -604,7 +604,7 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   // launches the norm for its copy as well and takes the same product.
   auto norm_gemm = [&](int kind, const void* g, const void* b, int prior_site, const void* W, int N,
                        int epi, const void* bias, void* out, int ldo) {
-    const bool fused = prior_site < 0 && gemm_takes_norm(m->dtype, T, d, normk);
+    const bool fused = prior_site < 0 && gemm_takes_norm(m->dtype, T, N, d, epi, normk);
     if (!fused || (dump && kind != GM_K_GEMM_HEAD)) norm_rows(hh, aa, g, b, prior_site);
     if (dump && kind != GM_K_GEMM_HEAD) dump->copy(cur_layer, kind == GM_K_GEMM_QKV ? 0 : 4, aa, s);
     const Norm n{g, b};

@@ -221,3 +221,14 @@ def test_decode_wide_head_on_matrix_cores(dtype, batch):
     w = synth.make_weights(cfg, 31)
     ids, mask = synth.make_inputs(cfg, 2, seq=56)       # room for the 4 steps in the cache
     decode_case(cfg, w, ids, mask, 4, cfg.seq, f"causal_lm_768 reduced {dtype} vocab 9001")
+
+
+@pytest.mark.parametrize("batch", [1, 2, 5])
+def test_decode_fp32_lane_sums(batch):
+    """fp32 steps of 1, 2 and 5 sequences, d 768: the new keys and values of one
+    or two sequences are appended by the lane-sum product."""
+    cfg = synth.reduced("causal_lm_768").replace(n_layers=2, vocab=9001, batch=batch, seq=40,
+                                                 max_pad=8, dtype="f32")
+    w = synth.make_weights(cfg, 31)
+    ids, mask = synth.make_inputs(cfg, 2, seq=36)
+    decode_case(cfg, w, ids, mask, 4, cfg.seq, f"causal_lm_768 reduced fp32 batch {batch}")

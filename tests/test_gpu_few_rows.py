@@ -2,7 +2,8 @@
 forward): every way the norm of the input rows is taken (into LDS, scaled
 after the product, by its own launch), row counts from 1 to 16, column counts
 that leave a partial group of 16, and the plain, gated and rotary epilogues,
-for each storage type.  Logits over every position against the oracle (fp32
+for each storage type; fp32 products of at most 8 rows that are summed across
+the lanes.  Logits over every position against the oracle (fp32
 1e-4, 16-bit 2e-2).  A debug forward, which also stores the norms' outputs,
 gives the logits and the residual stream of the ordinary forward bit for bit.
 """
@@ -44,6 +45,17 @@ def test_layernorm_of_long_rows(dtype):
     _compare(synth.reduced("causal_lm_768").replace(
         n_layers=2, d_model=1152, n_heads=9, d_ff=704, batch=2, seq=7, vocab=515, max_pad=3,
         dtype=dtype))
+
+
+@pytest.mark.parametrize("batch,seq", [(1, 1), (2, 1), (1, 3), (4, 1), (1, 5), (2, 4), (3, 3)])
+@pytest.mark.parametrize("d,ff,vocab", [(768, 1344, 9001), (832, 2112, 8193), (512, 1280, 8192)])
+def test_fp32_lane_sums(d, ff, vocab, batch, seq):
+    """1, 2, 3-4, 5-8 and 9 rows: a head of 8192 and more columns (the last
+    group partial), outputs of 2048 and more and of fewer columns, K from 512
+    to 2112; bias, GELU and residual."""
+    _compare(synth.reduced("causal_lm_768").replace(
+        n_layers=1, d_model=d, n_heads=d // 64, d_ff=ff, batch=batch, seq=seq, vocab=vocab,
+        max_pad=min(1, seq - 1), dtype="f32"))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])

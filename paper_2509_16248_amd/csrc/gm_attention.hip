@@ -207,7 +207,8 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
 // ------------------------------------------------------------ reference kernel
 // One wavefront per (query, head, sequence): scores in LDS, two passes for
 // max and sum, then one output channel per lane.  Used for the 16-bit head
-// size the MFMA kernel does not cover (32).
+// size the MFMA kernel does not cover (32), and in fp32 for so few keys that the
+// MFMA kernel's merge costs more than they do.
 template <typename T>
 __global__ __launch_bounds__(64) void k_attn_rows(AttnArgs a) {
   extern __shared__ float sm[];
@@ -608,7 +609,10 @@ static void launch_flash_ord(const AttnArgs& a, dim3 grid, hipStream_t s) {
 void launch_attention(const AttnArgs& a, hipStream_t s) {
   const bool mfma_ok = a.dtype != kF32 && (a.hd == 64 || a.hd == 128);
   if (!mfma_ok) {
-    if (a.dtype == kF32) {
+    // fp32, up to 6 keys (us a launch, rows / k_attn_f32, head size 64: 1 key
+    // 4.5 / 6.5, 4 keys 4.8 / 7.2, 6 keys 4.4 / 7.4; head size 32, 6 keys 5.2 /
+    // 5.2; whole forwards of 8 keys are equal, of 12 slower by 1 - 3%)
+    if (a.dtype == kF32 && a.Sk > 6) {
       const dim3 grid((a.Sq + 31) / 32, a.H, a.B), block(256);
       if (a.hd == 32) hipLaunchKernelGGL(k_attn_f32<32>, grid, block, 0, s, a);
       else if (a.hd == 64) hipLaunchKernelGGL(k_attn_f32<64>, grid, block, 0, s, a);
@@ -617,7 +621,8 @@ void launch_attention(const AttnArgs& a, hipStream_t s) {
     }
     const dim3 grid(a.Sq, a.H, a.B);
     const size_t lds = (a.hd + a.Sk) * sizeof(float);
-    if (a.dtype == kBF16) hipLaunchKernelGGL(k_attn_rows<bf16_t>, grid, dim3(64), lds, s, a);
+    if (a.dtype == kF32) hipLaunchKernelGGL(k_attn_rows<float>, grid, dim3(64), lds, s, a);
+    else if (a.dtype == kBF16) hipLaunchKernelGGL(k_attn_rows<bf16_t>, grid, dim3(64), lds, s, a);
     else hipLaunchKernelGGL(k_attn_rows<f16_t>, grid, dim3(64), lds, s, a);
     return;
   }

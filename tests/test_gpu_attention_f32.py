@@ -1,8 +1,9 @@
 """GPU parity of fp32 attention (tiles of 32 queries x 32 keys, keys split over
-4 wavefronts) at the edges of its tiles: sequence lengths around 32 and 128,
-each head size, causal and bidirectional, with and without padded keys (up to
-all but one key of a sequence), and cross-attention with unequal lengths.
-Logits over every position against the oracle at 1e-4.
+4 wavefronts; a wavefront per query for up to 6 keys) at the edges of its tiles:
+sequence lengths around 6, 32 and 128, each head size, causal and bidirectional,
+with and without padded keys (up to all but one key of a sequence), and
+cross-attention with unequal lengths.  Logits over every position against the
+oracle at 1e-4.
 
 A token whose key and value rows are NaN does not reach a query that may not
 see it: the logits of those queries are those of a run with a finite token in
@@ -23,7 +24,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("heads", [8, 4, 2])
-@pytest.mark.parametrize("batch,seq,pad", [(1, 1, 0), (2, 31, 30), (2, 33, 0), (3, 129, 128),
+@pytest.mark.parametrize("batch,seq,pad", [(1, 1, 0), (3, 6, 4), (2, 7, 3), (2, 31, 30), (2, 33, 0), (3, 129, 128),
                                            (1, 160, 40)])
 def test_tiles(causal, heads, batch, seq, pad):
     _compare(synth.reduced("causal_lm_768").replace(
@@ -31,7 +32,7 @@ def test_tiles(causal, heads, batch, seq, pad):
         max_pad=pad, causal=causal, dtype="f32"))
 
 
-@pytest.mark.parametrize("src,tgt", [(65, 7), (40, 33)])
+@pytest.mark.parametrize("src,tgt", [(65, 7), (40, 33), (6, 6), (7, 5)])
 def test_cross_attention(src, tgt):
     cfg = synth.reduced("seq2seq_768").replace(
         n_layers=1, n_dec_layers=1, d_model=128, n_heads=2, d_ff=192, batch=2, seq=src, tgt_seq=tgt,
@@ -55,7 +56,7 @@ def _same(got, ref):
 
 
 @pytest.mark.parametrize("heads", [8, 4, 2])
-@pytest.mark.parametrize("seq,bad", [(3, 2), (40, 39), (40, 5), (150, 90), (150, 149)])
+@pytest.mark.parametrize("seq,bad", [(3, 2), (7, 4), (40, 39), (40, 5), (150, 90), (150, 149)])
 def test_nan_at_a_later_position(heads, seq, bad):
     cfg = synth.reduced("decoder_4096").replace(
         n_layers=2, d_model=256, n_heads=heads, d_ff=256, batch=2, seq=seq, vocab=300, dtype="f32")

@@ -567,10 +567,15 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   da.part = m->dpart;
   {
     // Split the keys only when there are fewer than ~100 (sequence, head)
-    // pairs to spread over the GPU and the cache is longer than four round
-    // trips of a workgroup's loads (keys_per_trip): a split costs a merge
-    // launch of 4.8 us, a round trip about 1.5 (measured: splitting 8 x 12
-    // heads further is no faster); chunks are a multiple of 64 keys.
+    // pairs to spread over the GPU (splitting 8 x 12 heads further is no
+    // faster) and the cache is longer than four round trips of a workgroup's
+    // loads (keys_per_trip): a split costs a merge launch of 4.8 us.  With every
+    // position in use the two sides meet at two to three trips (us a step, split
+    // / one chunk: 1 x 12 heads of 64, 4 layers, 2 trips 168 / 155, 3 trips 168 /
+    // 164, 4 trips 169 / 174; 2 x 12 heads 161 / 158, 164 / 167, 165 / 179; 1 x 32
+    // heads of 128, 2 layers, 2 trips 310 / 309, 4 trips 318 / 322), but a
+    // step knows the capacity only, and a cache in use is half full on average.
+    // Chunks are a multiple of 64 keys.
     const int keys_per_trip = static_cast<int>(65536 / (hd * m->esz));
     int want = (96 + B * c.n_heads - 1) / (B * c.n_heads);
     want = want < m->dec_nsplit ? want : m->dec_nsplit;

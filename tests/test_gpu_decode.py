@@ -232,3 +232,51 @@ def test_decode_fp32_lane_sums(batch):
     w = synth.make_weights(cfg, 31)
     ids, mask = synth.make_inputs(cfg, 2, seq=36)
     decode_case(cfg, w, ids, mask, 4, cfg.seq, f"causal_lm_768 reduced fp32 batch {batch}")
+
+
+# cache, head size, storage type: a little over four round trips of a workgroup's
+# loads, which split the keys of a (sequence, head) over workgroups
+@pytest.mark.parametrize("name,dtype,hd,max_seq", [
+    ("decoder_4096", "bf16", 128, 1100), ("decoder_4096", "f16", 128, 1089),
+    ("decoder_4096", "f32", 128, 577), ("causal_lm_768", "bf16", 64, 2100),
+    ("causal_lm_768", "f32", 64, 1025), ("decoder_4096", "f32", 32, 2113)])
+@pytest.mark.parametrize("batch,heads", [(1, 1), (3, 2)])
+def test_decode_split_keys(name, dtype, hd, max_seq, batch, heads):
+    """Few (sequence, head) pairs on a long cache: chunks past the last key, a
+    partial last chunk, one short prompt whose keys all lie in the first
+    chunks."""
+    cfg = synth.reduced(name).replace(
+        n_layers=1, d_model=64 * ((heads * hd + 63) // 64), n_heads=heads, d_ff=128, vocab=300,
+        batch=batch, seq=max_seq, max_pad=0, dtype=dtype)
+    cfg = cfg.replace(n_heads=cfg.d_model // hd)
+    if cfg.pos == "rotary":
+        cfg = cfg.replace(rope_capacity=max_seq)
+    w = synth.make_weights(cfg, 22)
+    ids, mask = synth.make_inputs(cfg, 5, seq=max_seq - 3)
+    if batch > 1:
+        mask[1, 70:] = 0
+        mask[2, max_seq - 60:] = 0
+        mask[0, 128:256] = 0               # a whole chunk of hidden keys
+    m = decode_case(cfg, w, ids, mask, 3, max_seq, f"{name} {dtype} split keys")
+    # the merge of the chunks is a launch that a shorter cache does without
+    split = m.stats()["kernels_per_forward"]
+    m.close()
+    m = gpu_model(cfg.replace(seq=64), w, max_seq=64, kv_cache=True)
+    run(m, ids[:, :60], np.ones_like(mask[:, :60]))
+    decode(m, [1] * batch)
+    assert split == m.stats()["kernels_per_forward"] + 1
+    m.close()
+
+
+@pytest.mark.parametrize("name", ["causal_lm_768", "decoder_4096"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("batch", [16, 17, 33])
+def test_decode_many_sequences(name, dtype, batch):
+    """More than 16 sequences take the tiled products, which append the new keys
+    and values from 32 x 32 accumulator tiles (with bias, and rotated); the
+    steps read the appended keys back."""
+    cfg = synth.reduced(name).replace(n_layers=2, d_model=192, n_heads=3, d_ff=320, vocab=515,
+                                      batch=batch, seq=28, max_pad=12, dtype=dtype)
+    w = synth.make_weights(cfg, 23)
+    ids, mask = synth.make_inputs(cfg, 5, seq=24)
+    decode_case(cfg, w, ids, mask, 4, cfg.seq, f"{name} {dtype} batch {batch}")

@@ -1,10 +1,9 @@
-"""GPU parity for the kernel paths the five workloads do not reach, so that
-every kernel libgm can launch runs under a test:
+"""GPU parity for kernel paths the five workloads do not reach:
 
-* the large-tile GEMM in fp16 (128x384, 128x256 and 256x256 tiles: a
+* the large-tile GEMM in fp16 (256x192, 256x128 and 256x256 tiles: a
   one-layer fp16 model of the 4096-wide decoder's shape), and a 2048-wide
-  model whose products take other tile choices (gate/up: 352 tiles of
-  256x256), in bf16 and fp16;
+  model whose products take other tile choices (QKV and gate/up 256x192, O and
+  down 128x128), in bf16 and fp16;
 * attention of 16-bit models with head size 32 (the row kernel);
 * causal attention with key lengths cut short by long padding, in bf16
   and fp16;
@@ -38,15 +37,15 @@ def _compare(cfg, seed=3):
 
 
 def test_large_tile_gemm_fp16():
-    """QKV 2048x12288x4096 (128x384 tiles, rotary), O and down (128x256),
-    gate/up and head (256x256, K step 64 in two stages), in fp16."""
+    """QKV 2048x12288x4096 (256x192 tiles, rotary), O and down (256x128),
+    gate/up and head (256x256), in fp16."""
     _compare(synth.preset("decoder_4096", n_layers=1, dtype="f16"))
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_large_tile_gemm_k64_two_stages(dtype):
-    """d 2048, SwiGLU 5632: gate/up 2048x11264x2048 gives 352 tiles of
-    256x256 (1.375 waves); QKV 2048x6144 takes 128x384; K of 2048."""
+    """d 2048, SwiGLU 5632: gate/up 2048x11264x2048 gives 472 tiles of 256x192
+    and QKV 2048x6144 256 of them; O and down 128x128; the head 256x256."""
     cfg = synth.preset("decoder_4096", n_layers=1, d_model=2048, n_heads=16, d_ff=5632,
                        dtype=dtype)
     _compare(cfg)

@@ -31,6 +31,17 @@ def test_rows_and_odd_vocabulary(dtype, batch, seq, vocab):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("name", ["causal_lm_768", "decoder_4096"])
+@pytest.mark.parametrize("batch,seq,vocab", [(1, 19, 333), (1, 257, 2050), (7, 256, 9001),
+                                             (8, 256, 9001)])
+def test_one_stage(name, dtype, batch, seq, vocab):
+    """K of 64: the ring holds a single stage (16-bit)."""
+    _compare(synth.reduced(name).replace(
+        n_layers=1, d_model=64, n_heads=1, d_ff=64, batch=batch, seq=seq, vocab=vocab,
+        max_pad=0, dtype=dtype))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("heads", [2, 4, 8])
 @pytest.mark.parametrize("batch,seq", [(1, 19), (3, 43), (5, 130)])
 def test_rotary_and_gated(dtype, heads, batch, seq):

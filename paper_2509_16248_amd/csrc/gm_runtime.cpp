@@ -438,7 +438,6 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   P(GM_K_EMBED, -1, 0.0, static_cast<double>(T) * d * es * (c.pos == GM_POS_LEARNED ? 3 : 2));
   r.ids = nullptr;
 
-  const int nb = B;
   char* hh = static_cast<char*>(wk.h);
   char* aa = static_cast<char*>(wk.a);
   char* qq = static_cast<char*>(wk.qkv);
@@ -515,7 +514,7 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
 
   AttnArgs at{};
   at.dtype = m->dtype;
-  at.B = nb;
+  at.B = B;
   at.Sq = at.Sk = S;
   at.H = c.n_heads;
   at.hd = hd;
@@ -538,7 +537,7 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   const int up_n = c.ffn == GM_FFN_GELU ? ff : 2 * ff;
   const int qkv_epi = c.pos == GM_POS_ROTARY ? kEpiRope : kEpiStore;
   const double pairs = c.causal ? 0.5 * S * (S + 1.0) : static_cast<double>(S) * S;
-  const double attn_flops = 4.0 * hd * pairs * nb * c.n_heads;
+  const double attn_flops = 4.0 * hd * pairs * B * c.n_heads;
   const double attn_bytes = es * (static_cast<double>(T) * 3 * d + static_cast<double>(T) * d);
   KvArgs kv{};
   kv.dtype = m->dtype;
@@ -555,7 +554,7 @@ void enqueue(gm_model* m, int B, int S, const int32_t* ids, const int32_t* mask,
   kv.max_seq = c.max_seq;
   DecAttnArgs da{};
   da.dtype = m->dtype;
-  da.B = nb;
+  da.B = B;
   da.H = c.n_heads;
   da.hd = hd;
   da.d = d;
@@ -714,7 +713,6 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
     P(GM_K_PROLOGUE, -1, 0.0, 8.0 * Tt);
     brk(kCutGuardsTgt);   // original program: the target's guards and mask.any() read on the host
   };
-  const int Tsp = Ts, Ttp = Tt, nb = B;
   char* hh = static_cast<char*>(m->h);
   char* aa = static_cast<char*>(m->a);
   char* qq = static_cast<char*>(m->qkv);
@@ -723,11 +721,6 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
   char* mm = static_cast<char*>(m->mem);
   char* kk = static_cast<char*>(m->kvc);
   char* qcc = static_cast<char*>(m->qc);
-  char* lg = static_cast<char*>(logits);
-  const int32_t* sids = src_ids;
-  const int32_t* tids = tgt_ids;
-  const int32_t* smask = src_mask;
-  const int32_t* tmask = tgt_mask;
   RowArgs r{};
   r.dtype = m->dtype;
   r.d = d;
@@ -790,7 +783,7 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
   };
   AttnArgs at{};
   at.dtype = m->dtype;
-  at.B = nb;
+  at.B = B;
   at.H = c.n_heads;
   at.hd = hd;
   at.d = d;
@@ -813,8 +806,8 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
     a.causal = causal;
     if (on()) launch_attention(a, s);
     const double pairs = causal ? 0.5 * Sq * (Sq + 1.0) : static_cast<double>(Sq) * Sk;
-    P(kind, cur_layer, 4.0 * hd * pairs * nb * c.n_heads,
-      es * (static_cast<double>(nb) * Sq * 2 * d + static_cast<double>(nb) * Sk * 2 * d));
+    P(kind, cur_layer, 4.0 * hd * pairs * B * c.n_heads,
+      es * (static_cast<double>(B) * Sq * 2 * d + static_cast<double>(B) * Sk * 2 * d));
   };
   const int up_epi = c.ffn == GM_FFN_GELU ? kEpiGelu
                      : c.ffn == GM_FFN_GEGLU ? kEpiGatedGelu : kEpiGatedSilu;
@@ -827,47 +820,47 @@ void enqueue_seq2seq(gm_model* m, int B, int Ss, const int32_t* src_ids, const i
   };
 
   // encoder (bidirectional; the source's padding branch)
-  embed(Tsp, Ss, sids, m->enc_pos_emb);
+  embed(Ts, Ss, src_ids, m->enc_pos_emb);
   for (int l = 0; l < c.n_layers; ++l) {
     cur_layer = l;
     const LayerBufs& L = m->layers[l];
-    norm_rows(Tsp, hh, aa, L.ln1_g, L.ln1_b);
-    gemm(GM_K_GEMM_QKV, Tsp, aa, d, L.wqkv, 3 * d, kEpiStore, L.bqkv, qq, 3 * d, nullptr);
-    attention(GM_K_ATTENTION, Ss, Ss, qkv, 3 * d, qkv + d * m->esz, 3 * d, smask, kPadAny,
+    norm_rows(Ts, hh, aa, L.ln1_g, L.ln1_b);
+    gemm(GM_K_GEMM_QKV, Ts, aa, d, L.wqkv, 3 * d, kEpiStore, L.bqkv, qq, 3 * d, nullptr);
+    attention(GM_K_ATTENTION, Ss, Ss, qkv, 3 * d, qkv + d * m->esz, 3 * d, src_mask, kPadAny,
               kKvLenBase, 0);
-    gemm(GM_K_GEMM_O, Tsp, cc, d, L.wo, d, kEpiResid, L.bo, hh, d, hh);
-    block_ffn(Tsp, L);
+    gemm(GM_K_GEMM_O, Ts, cc, d, L.wo, d, kEpiResid, L.bo, hh, d, hh);
+    block_ffn(Ts, L);
   }
   cur_layer = -1;
-  norm_rows(Tsp, hh, mm, m->enc_lnf_g, m->enc_lnf_b);
+  norm_rows(Ts, hh, mm, m->enc_lnf_g, m->enc_lnf_b);
   // k | v of every decoder layer from the encoder output, one GEMM
-  gemm(GM_K_GEMM_XKV, Tsp, mm, d, m->wkv_all, nd * 2 * d, kEpiStore, m->bkv_all, kk,
+  gemm(GM_K_GEMM_XKV, Ts, mm, d, m->wkv_all, nd * 2 * d, kEpiStore, m->bkv_all, kk,
        nd * 2 * d, nullptr);
 
   // decoder (causal self-attention under the target's padding branch,
   // cross-attention under the source's); its inputs' guards merge into the
   // forward's trap word
   target_prologue(s);
-  embed(Ttp, St, tids, m->pos_emb);
+  embed(Tt, St, tgt_ids, m->pos_emb);
   for (int l = 0; l < nd; ++l) {
     cur_layer = c.n_layers + l;
     const LayerBufs& L = m->dec_layers[l];
     const CrossBufs& X = m->dec_cross[l];
-    norm_rows(Ttp, hh, aa, L.ln1_g, L.ln1_b);
-    gemm(GM_K_GEMM_QKV, Ttp, aa, d, L.wqkv, 3 * d, kEpiStore, L.bqkv, qq, 3 * d, nullptr);
-    attention(GM_K_ATTENTION, St, St, qkv, 3 * d, qkv + d * m->esz, 3 * d, tmask, kPadAnyTgt,
+    norm_rows(Tt, hh, aa, L.ln1_g, L.ln1_b);
+    gemm(GM_K_GEMM_QKV, Tt, aa, d, L.wqkv, 3 * d, kEpiStore, L.bqkv, qq, 3 * d, nullptr);
+    attention(GM_K_ATTENTION, St, St, qkv, 3 * d, qkv + d * m->esz, 3 * d, tgt_mask, kPadAnyTgt,
               kKvLenBase + c.max_batch, 1);
-    gemm(GM_K_GEMM_O, Ttp, cc, d, L.wo, d, kEpiResid, L.bo, hh, d, hh);
-    norm_rows(Ttp, hh, aa, X.lnc_g, X.lnc_b);
-    gemm(GM_K_GEMM_XQ, Ttp, aa, d, X.wq, d, kEpiStore, X.bq, qcc, d, nullptr);
+    gemm(GM_K_GEMM_O, Tt, cc, d, L.wo, d, kEpiResid, L.bo, hh, d, hh);
+    norm_rows(Tt, hh, aa, X.lnc_g, X.lnc_b);
+    gemm(GM_K_GEMM_XQ, Tt, aa, d, X.wq, d, kEpiStore, X.bq, qcc, d, nullptr);
     attention(GM_K_XATTN, St, Ss, qcc, d, static_cast<char*>(kk) + static_cast<size_t>(l) * 2 * d * m->esz,
-              nd * 2 * d, smask, kPadAny, kKvLenBase, 0);
-    gemm(GM_K_GEMM_XO, Ttp, cc, d, X.wo, d, kEpiResid, X.bo, hh, d, hh);
-    block_ffn(Ttp, L);
+              nd * 2 * d, src_mask, kPadAny, kKvLenBase, 0);
+    gemm(GM_K_GEMM_XO, Tt, cc, d, X.wo, d, kEpiResid, X.bo, hh, d, hh);
+    block_ffn(Tt, L);
   }
   cur_layer = -1;
-  norm_rows(Ttp, hh, aa, m->lnf_g, m->lnf_b);
-  gemm(GM_K_GEMM_HEAD, Ttp, aa, d, m->head, c.vocab, kEpiStore, nullptr, lg, c.vocab, nullptr);
+  norm_rows(Tt, hh, aa, m->lnf_g, m->lnf_b);
+  gemm(GM_K_GEMM_HEAD, Tt, aa, d, m->head, c.vocab, kEpiStore, nullptr, logits, c.vocab, nullptr);
   if (on()) launch_emit_effects(m->state, m->fifo, kFifoCap, 0, nullptr, nullptr, 0, 0, B, 1, Finish{}, s);
   P(GM_K_EFFECTS, -1, 0.0, 0.0);
 }

@@ -58,7 +58,9 @@ __device__ __forceinline__ void store4(T* p, const float* v, int nvalid, bool ve
 // x * Phi(x).  fp32 models: through erff.  16-bit models: Phi through
 // erfc(z) = t Q(t) exp(-z^2) with t = 1 / (1 + 0.3 |x|) on the hardware
 // reciprocal and exponential; Q is a degree-7 minimax fit of
-// erfcx(|x| / sqrt 2) / (2 t), relative error 1.5e-7 (no cancellation on the
+// erfcx(|x| / sqrt 2) / (2 t), relative error 1.5e-7.  In fp32 the whole is
+// within 5e-7 below 1 and, as the exponent is rounded, 4e-6 at 9 and 7e-6 at
+// 12, far below a 16-bit rounding (no cancellation on the
 // negative side, where 1 + erff loses digits), 17 vector instructions against
 // about 45: 4096 x 3072 x 768 with GELU 34.9 -> 29.2 us together with the
 // per-wavefront staging of the epilogue.

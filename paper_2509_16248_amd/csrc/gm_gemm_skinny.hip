@@ -118,8 +118,10 @@ enum RowsNorm : int {
 //    are on their way (8 x 2304 x 768: 3.7 -> 4.7 us; for longer rows the wait
 //    costs more than the launch: 1 x 22016 x 4096 42 -> 57 us);
 //  - a longer RMSNorm does not come before the product at all: its gain is
-//    multiplied into the rows (one rounding, as before), every wavefront sums
-//    the squares of the elements it reads, and the finished sums are scaled.
+//    multiplied into the rows (one rounding, as in a norm of its own), every
+//    wavefront sums the squares of the elements it reads, and the finished sums
+//    are scaled.  (Rows whose squares leave fp32 give 0 either way as long as
+//    x g and the sums stay inside it, |x| up to about 1e36.)
 // Against kernels of vector instructions that streamed whole weight rows:
 // 8 x 22016 x 4096 87 -> 46 us, 8 x 2304 x 768 7.0 -> 3.5, 1 x 12288 x 4096 31 -> 27.
 template <typename T, int CT, int NORM>

@@ -174,17 +174,17 @@ def breakdown(prof):
 
 def measured_traffic(workload):
     """HBM bytes per GEMM launch from the committed rocprofv3 FETCH_SIZE /
-    WRITE_SIZE record of this workload, if it was taken on the GEMM source as
-    it is now."""
-    import hashlib
+    WRITE_SIZE record of this workload, if it was taken on the GEMM sources as
+    they are now."""
+    from paper_2509_16248_amd.prof_summary import gemm_sources_sha256
     path = os.path.join(ROOT, "profiles", f"gemm_traffic_{workload}.json")
-    src = os.path.join(ROOT, "paper_2509_16248_amd", "csrc", "gm_gemm_tile.h")
     try:
         rec = json.load(open(path))
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
     except OSError:
         return None
-    return rec["traffic_bytes_per_launch"] if rec.get("gm_gemm_hip_sha256") == sha else None
+    if rec.get("gemm_sources_sha256") != gemm_sources_sha256():
+        return None
+    return rec["traffic_bytes_per_launch"]
 
 
 def load_model(name, seed=WEIGHT_SEED):

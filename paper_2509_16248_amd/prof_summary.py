@@ -12,9 +12,9 @@ Calibration: both runs contain the runtime's copy kernel moving a weight of
 known size into library memory (the token embedding: vocab x d_model x 2
 bytes); the largest such dispatch gives the bytes each counter unit stands
 for (FETCH_SIZE of a copy counts half its bytes on this GPU, WRITE_SIZE all
-of them).  The record carries the SHA-256 of gm_gemm_tile.h so that a stale
-measurement is not reported after the kernel changes.  Prints a markdown
-table as well.
+of them).  The record carries a SHA-256 over the GEMM sources (csrc/gm_gemm*:
+kernels, epilogues, tile shapes and their choice) so that a stale measurement is
+not reported after any of them changes.  Prints a markdown table as well.
 """
 from __future__ import annotations
 
@@ -54,6 +54,19 @@ WORKLOADS = {
 }
 
 
+CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
+
+
+def gemm_sources_sha256(csrc=CSRC):
+    """SHA-256 over the names and contents of csrc/gm_gemm*."""
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(csrc, "gm_gemm*"))):
+        h.update(os.path.basename(path).encode() + b"\0")
+        with open(path, "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
+
+
 def _rows(d, counter):
     path = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
     if not path:
@@ -65,7 +78,7 @@ def _rows(d, counter):
     return out
 
 
-def summarize(workload, fetch_dir, write_dir, src):
+def summarize(workload, fetch_dir, write_dir):
     wl = WORKLOADS[workload]
     f, w = _rows(fetch_dir, "FETCH_SIZE"), _rows(write_dir, "WRITE_SIZE")
     copies_f = [v for k, _, v in f if k.startswith(COPY)]
@@ -97,7 +110,7 @@ def summarize(workload, fetch_dir, write_dir, src):
         e["write_kib_raw"] = round(wk, 1)
         del e["fetch_kib"], e["write_kib"]
     return {"workload": workload, "kernels": list(wl["kernels"]),
-            "gm_gemm_hip_sha256": hashlib.sha256(open(src, "rb").read()).hexdigest(),
+            "gemm_sources_sha256": gemm_sources_sha256(),
             "fetch_scale": round(fscale, 3), "write_scale": round(wscale, 3),
             "traffic_bytes_per_launch": int((tot_f + tot_w) / n),
             "fetch_bytes_per_launch": int(tot_f / n), "write_bytes_per_launch": int(tot_w / n),
@@ -107,8 +120,7 @@ def summarize(workload, fetch_dir, write_dir, src):
 def main(argv):
     if len(argv) != 4 or argv[0] not in WORKLOADS:
         raise SystemExit(__doc__)
-    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "gm_gemm_tile.h")
-    rec = summarize(argv[0], argv[1], argv[2], src)
+    rec = summarize(argv[0], argv[1], argv[2])
     with open(argv[3], "w") as fh:
         json.dump(rec, fh, indent=1)
     print(f"fetch scale {rec['fetch_scale']}, write scale {rec['write_scale']}")
